@@ -1,0 +1,436 @@
+// Fused step on a 1-bit block band for float32 states (every H and B), the
+// products of the fused step of Eq. 3 in the operand order of Algorithm 1:
+//   forward:  a[k]    = sum_e (sum_s bits[e][k][s] X[k-1+s]) W_e   (+ deg_e b_e)
+//   reverse:  dM_e[k] = sum_s bits_t[e][k][s] da[k-1+s]            (stored)
+//             dX[k]   = dX_in[k] + sum_e dM_e[k] W_e^T
+//
+// What bounds the aggregation in fp32 is the matrix-core rate: an fp32 k step
+// of 32 nodes takes eight v_mfma_f32_16x16x4_f32 of 32 cycles.  The band's
+// entries are 0 or 1, exact in bf16, so the states are split instead, once,
+// when they are staged: x = hi + mid + lo with bf16 parts (8 + 8 + 8
+// significant bits, cut off, so the split is exact), and a k step is three
+// v_mfma_f32_16x16x32_bf16 of 16 cycles with float accumulation: the same
+// sums of the same values at 5.3 times the rate.  The transform by W_e stays
+// on the fp32 instructions: there both operands have 24 bits.
+//
+// The transform's contraction over features is split into slices of HQ
+// features, (A_e X) W_e = sum_q (A_e X[:, q]) W_e[q, :]: per slice the three
+// node blocks' parts (3 x 3 B x HQ bf16) are staged once in LDS and reused by
+// every edge type, and the type loop has no barrier.
+//
+// Measured on 20,000 nodes, B = 128, H = 64, 10 types, per pass of two steps
+// forward and reverse: 1055 -> 439 us against the fp32 form that staged
+// 64-node chunks per type and multiplied them in fp32 (205 us per step launch
+// there); the distance from a 64-bit reference 1.6e-6 -> 1.3e-6 of the norm
+// (fewer roundings per sum).  Bound now by the transform's fp32 products.
+#include "device_common.h"
+#include "kernels.h"
+
+namespace ggnn {
+namespace dev {
+
+template <int H, int B, int WAVES, int TG>
+struct SplitCfg {
+  // Features per slice: as many as three parts of three blocks leave room for.
+  static constexpr int HQ = B >= 512 ? 16 : (B >= 128 || H == 32 || H == 256 ? 32 : 64);
+  static constexpr int NQ = H / HQ, MQ = HQ / 16, MT = H / 16;
+  static constexpr int RPW = 32, NTW = 2;        // rows per wave, 16-row tiles per wave
+  static constexpr int R = WAVES * RPW, NT = TG * WAVES * kWave;
+  static constexpr int RB = B / 32;              // bit-row bytes per lane and block (= k steps per block)
+  // k order of a block's columns (as in the bf16 step kernels): contiguous
+  // where a register transpose of the bit bytes exists (and trivially for one
+  // byte), so that empty k steps can be skipped; else lane group g holds
+  // columns g B/4 .. (g + 1) B/4 - 1.
+  static constexpr bool KCONT = RB == 1 || RB == 4 || RB == 8;
+  static constexpr int PLANE = 3 * B * HQ;       // elements of one part of the staged window
+  // The groups' partial sums meet in LDS, one row tile at a time.
+  static constexpr int RED = TG == 1 ? 0 : TG * WAVES * MT * 1024;
+  static constexpr int LDS = 3 * PLANE * 2 > RED ? 3 * PLANE * 2 : RED;
+  static constexpr int GM = MQ >= 4 || H == 256 ? 2 : 4;     // output tiles whose weights are loaded together
+};
+
+// x = hi + mid + lo, each with at most eight significant bits (the low words
+// of the returned floats are zero); an infinite x is its own hi part.
+__device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  hi = __float_as_uint(x) & 0xFFFF0000u;
+  float r = x - __uint_as_float(hi);
+  r = __builtin_isinf(x) ? 0.f : r;
+  mid = __float_as_uint(r) & 0xFFFF0000u;
+  lo = __float_as_uint(r - __uint_as_float(mid));
+}
+// Eight floats -> three bf16 fragments.
+__device__ __forceinline__ void split3x8(const float (&v)[8], u32x4 (&o)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t a[3], b[3];
+    split3(v[2 * i], a[0], a[1], a[2]);
+    split3(v[2 * i + 1], b[0], b[1], b[2]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) o[p][i] = __builtin_amdgcn_perm(b[p], a[p], 0x07060302u);   // the two high halves
+  }
+}
+
+__device__ __forceinline__ bf16x8 split_bits_frag(uint32_t byte) {   // bit i -> element i (0 or 1)
+  const uint32_t x = byte * 0x8001u;
+  u32x4 w;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = (x & (0x10001u << (2 * k))) * (0x3F80u >> (2 * k));
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+template <int NB> struct SplitBits {
+  static constexpr int NW = NB < 4 ? 1 : NB / 4;
+  uint32_t w[NW];
+  __device__ __forceinline__ void load(const uint8_t* p) {
+    if constexpr (NB == 1) {
+      w[0] = *p;
+    } else if constexpr (NB == 2) {
+      w[0] = *reinterpret_cast<const uint16_t*>(p);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NW; ++i) w[i] = reinterpret_cast<const uint32_t*>(p)[i];
+    }
+  }
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int i = 0; i < NW; ++i) w[i] = 0u;
+  }
+  __device__ __forceinline__ uint32_t any() const {
+    uint32_t a = 0u;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) a |= w[i];
+    return a;
+  }
+  __device__ __forceinline__ uint32_t byte(int i) const { return (w[i / 4] >> (8 * (i % 4))) & 0xFFu; }
+  __device__ __forceinline__ int popc() const {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) c += __popc(w[i]);
+    return c;
+  }
+};
+
+__device__ __forceinline__ bool split_any(uint32_t x) { return __builtin_amdgcn_ballot_w64(x != 0u) != 0; }
+
+// Workgroup: R = 32 WAVES rows of block row k, TG * WAVES waves; wave w takes
+// rows 32 (w % WAVES) .. + 31 and the edge types of group w / WAVES (a
+// contiguous range).  V = X (forward, [n_pad][H]) or da (reverse,
+// [H][n_pad]); W [E][H][H]; Wt = W_e^T or NULL (forward).
+template <int H, int B, int WAVES, int TG, bool REV>
+__global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
+    const uint8_t* __restrict__ bits, const float* __restrict__ V, const float* __restrict__ W,
+    const float* __restrict__ Wt, const float* __restrict__ bias, float* out, int n_pad, int E, const float* dX_in,
+    float* __restrict__ dM, long ldm) {
+  using C = SplitCfg<H, B, WAVES, TG>;
+  constexpr int NT = C::NT, HQ = C::HQ, NQ = C::NQ, MQ = C::MQ, MT = C::MT, NTW = C::NTW, RB = C::RB, GM = C::GM;
+  constexpr int ROWB = B / 8, TPR = B / C::R;
+  static_assert(C::LDS <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(16))) char lds[C::LDS];
+  bf16s* const xs = reinterpret_cast<bf16s*>(lds);   // [part][block s][fragment order]
+
+  const int nb = n_pad / B;
+  const int t = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int k = t / TPR;
+  const int tid = threadIdx.x, lane = tid % kWave, wave = (tid / kWave) % WAVES, tg = tid / (WAVES * kWave);
+  const int q = lane % 16, g = lane / 16;
+  const int rw = (t % TPR) * C::R + C::RPW * wave;
+  const int s_lo = (k == 0) ? 1 : 0, s_hi = (k == nb - 1) ? 1 : 2;
+  const int e_lo = tg * E / TG, e_hi = (tg + 1) * E / TG;
+
+  auto load_bits = [&](int e, SplitBits<RB> (&dst)[3][NTW]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const uint8_t* p = bits + ((((size_t)e * nb + k) * 3 + s) * B + rw + q) * ROWB + g * RB;
+#pragma unroll
+      for (int n = 0; n < NTW; ++n) {
+        if (s < s_lo || s > s_hi) {
+          dst[s][n].zero();
+        } else {
+          dst[s][n].load(p + (size_t)16 * n * ROWB);
+        }
+      }
+    }
+  };
+
+  // One slice of the three blocks: a unit is eight nodes of four features
+  // (forward: eight 16-byte row loads) or of one feature (reverse).
+  auto stage = [&](int qs) __attribute__((always_inline)) {
+    auto put = [&](int s, int f, int c, const float (&v)[8]) __attribute__((always_inline)) {
+      const int kk = C::KCONT ? c / 32 : (c % (B / 4)) / 8, gg = C::KCONT ? (c / 8) % 4 : c / (B / 4);
+      u32x4 o[3];
+      split3x8(v, o);
+      bf16s* d = xs + s * B * HQ + fo<bf16s>(kk * MQ + f / 16, f % 16 + 16 * gg, 0);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(d + p * C::PLANE) = o[p];
+    };
+    if constexpr (!REV) {
+      constexpr int UB = (B / 8) * (HQ / 4);
+      for (int u = tid; u < 3 * UB; u += NT) {
+        const int s = u / UB, r = u % UB, f0 = 4 * (r % (HQ / 4)), c = 8 * (r / (HQ / 4));
+        if (s < s_lo || s > s_hi) continue;
+        f32x4 x[8];
+        const float* p = V + (size_t)((k - 1 + s) * B + c) * H + qs * HQ + f0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4*>(p + (size_t)i * H);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v[8] = {x[0][j], x[1][j], x[2][j], x[3][j], x[4][j], x[5][j], x[6][j], x[7][j]};
+          put(s, f0 + j, c, v);
+        }
+      }
+    } else {
+      constexpr int UB = (B / 8) * HQ;
+      for (int u = tid; u < 3 * UB; u += NT) {
+        const int s = u / UB, r = u % UB, f = 16 * (r / (16 * (B / 8))) + r % 16, c = 8 * ((r / 16) % (B / 8));
+        if (s < s_lo || s > s_hi) continue;
+        const float* p = V + (size_t)(qs * HQ + f) * n_pad + (k - 1 + s) * B + c;
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+        const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        put(s, f, c, v);
+      }
+    }
+  };
+
+  f32x4 acc[NTW][MT];
+#pragma unroll
+  for (int n = 0; n < NTW; ++n)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int qs = 0; qs < NQ; ++qs) {
+    SplitBits<RB> cur[3][NTW], nxt[3][NTW];
+    if (e_lo < e_hi) load_bits(e_lo, cur);
+    if (qs > 0) __syncthreads();   // every wave is done with the previous slice
+    stage(qs);
+    __syncthreads();
+    for (int e = e_lo; e < e_hi; ++e) {
+      if (e + 1 < e_hi) load_bits(e + 1, nxt);
+      // Weight fragments of output tiles mo (A operand: row = output feature
+      // 16 mo + q, k = the slice's features 16 m + 4 g + {0..3}).
+      auto load_w = [&](int mo, f32x4 (&wf)[MQ]) __attribute__((always_inline)) {
+        const int f = qs * HQ + 4 * g, o = 16 * mo + q;
+#pragma unroll
+        for (int m = 0; m < MQ; ++m) {
+          if (REV) {
+            wf[m] = *reinterpret_cast<const f32x4*>(W + ((size_t)e * H + o) * H + f + 16 * m);
+          } else if (Wt != nullptr) {
+            wf[m] = *reinterpret_cast<const f32x4*>(Wt + ((size_t)e * H + o) * H + f + 16 * m);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) wf[m][i] = W[((size_t)e * H + f + 16 * m + i) * H + o];
+          }
+        }
+      };
+      f32x4 wf[2][GM < MT ? GM : MT][MQ];
+      constexpr int GMT = GM < MT ? GM : MT;
+#pragma unroll
+      for (int i = 0; i < GMT; ++i) load_w(i, wf[0][i]);   // in flight during the aggregation
+
+      float fd[NTW];
+      if (!REV && bias != nullptr && qs == 0) {
+#pragma unroll
+        for (int n = 0; n < NTW; ++n) {
+          int d = cur[0][n].popc() + cur[1][n].popc() + cur[2][n].popc();
+          d += __shfl_xor(d, 16);
+          d += __shfl_xor(d, 32);
+          fd[n] = static_cast<float>(d);
+        }
+      }
+      f32x4 P[NTW][MQ];
+#pragma unroll
+      for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int m = 0; m < MQ; ++m) P[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const uint32_t godd = static_cast<uint32_t>(g & 1);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int n = 0; n < NTW; ++n) any |= cur[s][n].any();
+        if (!split_any(any)) continue;   // no edge of this type from the block into the wave's rows
+        if constexpr (RB == 4 || RB == 8) {
+#pragma unroll
+          for (int n = 0; n < NTW; ++n) bytes_to_contiguous<RB>(cur[s][n].w, godd);
+        }
+        const bf16s* xb = xs + s * B * HQ;
+#pragma unroll
+        for (int kk = 0; kk < RB; ++kk) {
+          if constexpr (C::KCONT && RB > 1) {
+            uint32_t step = 0u;
+#pragma unroll
+            for (int n = 0; n < NTW; ++n) step |= cur[s][n].byte(kk);
+            if (!split_any(step)) continue;
+          }
+          bf16x8 bf[NTW];
+#pragma unroll
+          for (int n = 0; n < NTW; ++n) bf[n] = split_bits_frag(cur[s][n].byte(kk));
+#pragma unroll
+          for (int p = 2; p >= 0; --p)   // the small parts first
+#pragma unroll
+            for (int m = 0; m < MQ; ++m) {
+              const bf16x8 af = load_fragi<bf16s>(xb + p * C::PLANE, kk * MQ + m, lane);
+#pragma unroll
+              for (int n = 0; n < NTW; ++n) mma(P[n][m], af, bf[n]);
+            }
+        }
+      }
+      if constexpr (REV) {
+#pragma unroll
+        for (int n = 0; n < NTW; ++n)
+#pragma unroll
+          for (int m = 0; m < MQ; ++m)
+            *reinterpret_cast<f32x4*>(dM + ((size_t)e * ldm + (size_t)k * B + rw + 16 * n + q) * H + qs * HQ +
+                                      16 * m + 4 * g) = P[n][m];
+      }
+      // acc[n][mo] += W rows x aggregate (accumulators straight as operands)
+#pragma unroll
+      for (int mo = 0; mo < MT; mo += GMT) {
+        const int b = (mo / GMT) & 1;
+        if (mo + GMT < MT) {
+#pragma unroll
+          for (int i = 0; i < GMT; ++i) load_w(mo + GMT + i, wf[1 - b][i]);
+        }
+#pragma unroll
+        for (int m = 0; m < MQ; ++m)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < GMT; ++i)
+#pragma unroll
+              for (int n = 0; n < NTW; ++n)
+                acc[n][mo + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[b][i][m][j], P[n][m][j], acc[n][mo + i], 0, 0, 0);
+      }
+      if (!REV && bias != nullptr && qs == 0) {
+#pragma unroll
+        for (int mo = 0; mo < MT; ++mo) {
+          const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + (size_t)e * H + 16 * mo + 4 * g);
+#pragma unroll
+          for (int n = 0; n < NTW; ++n)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[n][mo][j] += fd[n] * b4[j];
+        }
+      }
+      if (e + 1 < e_hi) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+          for (int n = 0; n < NTW; ++n) cur[s][n] = nxt[s][n];
+      }
+    }
+  }
+
+  // Output rows: lane (q, g) holds features 16 m + 4 g .. + 3 of row 16 n + q.
+  auto write = [&](int n, int m, f32x4 v) __attribute__((always_inline)) {
+    const size_t at = ((size_t)k * B + rw + 16 * n + q) * H + 16 * m + 4 * g;
+    if (REV && dX_in != nullptr) {
+      const f32x4 b = *reinterpret_cast<const f32x4*>(dX_in + at);
+      v = f32x4{b[0] + v[0], b[1] + v[1], b[2] + v[2], b[3] + v[3]};
+    }
+    *reinterpret_cast<f32x4*>(out + at) = v;
+  };
+  if constexpr (TG == 1) {
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) write(n, m, acc[n][m]);
+  } else {
+    // Per row tile: every group leaves its sums, then the groups share the
+    // output tiles (tile m by group m % TG), adding in group order.
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int n = 0; n < NTW; ++n) {
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < MT; ++m) red[((tg * WAVES + wave) * MT + m) * kWave + lane] = acc[n][m];
+      __syncthreads();
+      for (int m = tg; m < MT; m += TG) {
+        f32x4 v = red[(wave * MT + m) * kWave + lane];
+#pragma unroll
+        for (int gi = 1; gi < TG; ++gi) {
+          const f32x4 r = red[((gi * WAVES + wave) * MT + m) * kWave + lane];
+          v = f32x4{v[0] + r[0], v[1] + r[1], v[2] + r[2], v[3] + r[3]};
+        }
+        write(n, m, v);
+      }
+    }
+  }
+}
+
+}  // namespace dev
+
+#ifndef GGNN_SPLIT_SMALL_TILES
+#define GGNN_SPLIT_SMALL_TILES 512
+#endif
+namespace {
+struct SplitArgs {
+  bool rev;
+  const void *bits, *V, *W, *Wt;
+  const float* bias;
+  float* out;
+  const float* dX_in;
+  void* dM;
+  long ldm;
+  int n_pad, E;
+};
+
+template <int H, int B, int WAVES, int TG>
+hipError_t split_launch(const SplitArgs& A, hipStream_t st) {
+  using C = dev::SplitCfg<H, B, WAVES, TG>;
+  const dim3 grid((unsigned)(A.n_pad / C::R)), block(C::NT);
+  if (A.rev)
+    hipLaunchKernelGGL((dev::step_split_kernel<H, B, WAVES, TG, true>), grid, block, 0, st,
+                       static_cast<const uint8_t*>(A.bits), static_cast<const float*>(A.V),
+                       static_cast<const float*>(A.W), nullptr, nullptr, A.out, A.n_pad, A.E, A.dX_in,
+                       static_cast<float*>(A.dM), A.ldm);
+  else
+    hipLaunchKernelGGL((dev::step_split_kernel<H, B, WAVES, TG, false>), grid, block, 0, st,
+                       static_cast<const uint8_t*>(A.bits), static_cast<const float*>(A.V),
+                       static_cast<const float*>(A.W), static_cast<const float*>(A.Wt), A.bias, A.out, A.n_pad, A.E,
+                       nullptr, nullptr, 0L);
+  return hipGetLastError();
+}
+
+// Rows and type groups of a workgroup, by the number of 32-row tiles.  Few
+// tiles: one per workgroup and eight type groups, so that the compute units
+// fill up and a wave walks few types; many: more rows share a staged window.
+// The whole pass at H = 64, B = 128, 5 types with the small and the large
+// form: 112 / 145 us at 250 tiles, 154 / 161 us at 500, 246 / 205 us at 1000
+// (H = 32: 55 / 67, 65 / 72, 97 / 87; H = 128: 303 / 400, 405 / 437, 698 / 603).
+template <int H, int B>
+hipError_t split_pick(const SplitArgs& A, hipStream_t st) {
+  const int tiles = A.n_pad / 32;
+  if (tiles <= GGNN_SPLIT_SMALL_TILES) return split_launch<H, B, 1, 8>(A, st);
+  if constexpr (B == 32) return split_launch<H, B, 1, 2>(A, st);
+  if constexpr (B == 64) return split_launch<H, B, 2, 2>(A, st);
+  if constexpr (B >= 128) return split_launch<H, B, 4, 2>(A, st);
+}
+
+template <int H>
+hipError_t split_h(int B, const SplitArgs& A, hipStream_t st) {
+  switch (B) {
+    case 32: return split_pick<H, 32>(A, st);
+    case 64: return split_pick<H, 64>(A, st);
+    case 128: return split_pick<H, 128>(A, st);
+    case 256: return split_pick<H, 256>(A, st);
+    case 512: return split_pick<H, 512>(A, st);
+  }
+  return hipErrorInvalidValue;
+}
+}  // namespace
+
+namespace impl_f32 {
+hipError_t launch_step_split(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V, const void* W,
+                             const void* Wt, const float* bias, float* out, const float* dX_in, void* dM, long ldm,
+                             hipStream_t st) {
+  const SplitArgs A{rev, bits, V, W, Wt, bias, out, dX_in, dM, ldm, n_pad, E};
+  switch (H) {
+    case 32: return split_h<32>(B, A, st);
+    case 64: return split_h<64>(B, A, st);
+    case 128: return split_h<128>(B, A, st);
+    case 256: return split_h<256>(B, A, st);
+  }
+  return hipErrorInvalidValue;
+}
+}  // namespace impl_f32
+
+}  // namespace ggnn

@@ -141,6 +141,10 @@ hipError_t launch_step_bwd_bits_sn(int n_pad, int B, int H, int E, const void* b
 }
 namespace impl_f32 {
 GGNN_DT_LAUNCHERS
+// The fused bit-band step in fp32, forward (Wt = W_e^T or NULL) or reverse.
+hipError_t launch_step_split(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V, const void* W,
+                             const void* Wt, const float* bias, float* out, const float* dX_in, void* dM, long ldm,
+                             hipStream_t st);
 }
 #undef GGNN_DT_LAUNCHERS
 
@@ -166,7 +170,9 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 // 1-bit band: fused aggregate-first forward and transposed-band reverse.
 inline hipError_t launch_step_fwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits, const void* X,
                                        const void* W, const float* bias, float* a, hipStream_t st) {
-  return GGNN_DT_PICK(launch_step_fwd_bits, n_pad, B, H, E, bits, X, W, bias, a, st);
+  if (dt == GGNN_F32)
+    return impl_f32::launch_step_split(false, n_pad, B, H, E, bits, X, W, nullptr, bias, a, nullptr, nullptr, 0, st);
+  return impl_bf16::launch_step_fwd_bits(n_pad, B, H, E, bits, X, W, bias, a, st);
 }
 inline hipError_t launch_banded_bwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits_t, const void* da,
                                          void* dM, long ldm, hipStream_t st) {
@@ -189,8 +195,12 @@ inline hipError_t launch_step_fwd_bits_gru(int dt, int n_pad, int B, int H, int 
     if (fused) *fused = false;
     return impl_bf16::launch_step_wide(false, n_pad, B, H, E, bits, X, Wt, bias, a, nullptr, nullptr, 0, st);
   }
-  return GGNN_DT_PICK(launch_step_fwd_bits_gru, n_pad, B, H, E, bits, X, W, Wt, bias, a, Wi, U, bg, h_out, saved,
-                      fused, st);
+  if (dt == GGNN_F32) {
+    if (fused) *fused = false;
+    return impl_f32::launch_step_split(false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
+  }
+  return impl_bf16::launch_step_fwd_bits_gru(n_pad, B, H, E, bits, X, W, Wt, bias, a, Wi, U, bg, h_out, saved, fused,
+                                             st);
 }
 // Wt[e][o][h] = W[e][h][o].
 inline hipError_t launch_transpose_weights(int dt, int H, int E, const void* W, void* Wt, hipStream_t st) {
@@ -209,8 +219,13 @@ inline hipError_t launch_step_bwd_bits_gru(int dt, int n_pad, int B, int H, int 
     if (fused) *fused = false;
     return impl_bf16::launch_step_wide(true, n_pad, B, H, E, bits_t, da, W, nullptr, dX_out, dX_in, dM, ldm, st);
   }
-  return GGNN_DT_PICK(launch_step_bwd_bits_gru, n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, Wi, U, h_prev,
-                      saved_prev, da_prev, dh_prev, ghat_prev, fused, st);
+  if (dt == GGNN_F32) {
+    if (fused) *fused = false;
+    return impl_f32::launch_step_split(true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM, ldm,
+                                       st);
+  }
+  return impl_bf16::launch_step_bwd_bits_gru(n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, Wi, U, h_prev,
+                                             saved_prev, da_prev, dh_prev, ghat_prev, fused, st);
 }
 // Fused reverse step: dM_e = A_e^T da stored node-major (rows of type e start
 // at row e * ldm of dM), dX_out = dX_in (or 0) + sum_e dM_e W_e^T.
@@ -219,7 +234,10 @@ inline hipError_t launch_step_bwd_bits(int dt, int n_pad, int B, int H, int E, c
                                        hipStream_t st) {
   if (step_wide(dt, B, H))
     return impl_bf16::launch_step_wide(true, n_pad, B, H, E, bits_t, da, W, nullptr, dX_out, dX_in, dM, ldm, st);
-  return GGNN_DT_PICK(launch_step_bwd_bits, n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, st);
+  if (dt == GGNN_F32)
+    return impl_f32::launch_step_split(true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM, ldm,
+                                       st);
+  return impl_bf16::launch_step_bwd_bits(n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, st);
 }
 
 inline hipError_t launch_transform_fwd(int dt, int n_pad, int H, int E, const void* X, const void* W,

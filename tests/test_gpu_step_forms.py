@@ -1,0 +1,99 @@
+"""Launch forms of the device kernels at the sizes where their choice changes,
+against the CPU oracle: integer-valued inputs, where every partial sum is exact,
+are compared bitwise."""
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_helpers import say, dev, host, torch_dt
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+capi = pytest.importorskip("paper_1906_11786_amd.capi")
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    yield
+    torch.cuda.synchronize()
+
+
+def _edges(rng, n, m, E, span):
+    src = rng.integers(0, n, m)
+    dst = np.clip(src + rng.integers(-span, span + 1, m), 0, n - 1)
+    return src, dst, rng.integers(0, E, m)
+
+
+def _step_case(dt, B, H, E, nb, seed, bias):
+    """One forward and one reverse step (ggnn_step_bits_gru's aggregate, with and without W^T, and
+    ggnn_banded_step_bits_bwd), integers."""
+    rng = np.random.default_rng(seed)
+    n = B * nb
+    src, dst, et = _edges(rng, n, 3 * n, E, min(2 * B, 70))
+    bits, bits_t, _, _, _ = capi.ggnn_banded_pack_bits(n, E, B, src, dst, et)
+    s, d, e, _, _ = O.kept_edges(src, dst, et, B)
+    X = rng.integers(-2, 3, (n, H)).astype(np.float64)
+    W = rng.integers(-1, 2, (E, H, H)).astype(np.float64)
+    b = rng.integers(-2, 3, (E, H)).astype(np.float64) if bias else None
+    want = O.aggregate(n, s, d, e, O.msg_transform(X, W, b))
+    tb, tbt = torch.from_numpy(bits).cuda(), torch.from_numpy(bits_t).cuda()
+    Xt, Wt_, bt = dev(X, dt), dev(W, dt), None if b is None else dev(b)
+    a = torch.full((n, H), float("nan"), device="cuda")
+    capi.ggnn_banded_step_bits(dt, n, B, H, E, tb, Xt, Wt_, bt, a)
+    np.testing.assert_array_equal(host(a), want)
+    WT = dev(W.transpose(0, 2, 1), dt)
+    z = torch.zeros((H, 3 * H), device="cuda", dtype=torch_dt(dt))
+    ho, sv = torch.empty_like(Xt), torch.empty((n, 3 * H), device="cuda", dtype=torch_dt(dt))
+    a.fill_(float("nan"))
+    capi.ggnn_step_bits_gru(dt, n, B, H, E, tb, Xt, Wt_, WT, bt, z, z, torch.zeros(3 * H, device="cuda"), a, ho, sv)
+    np.testing.assert_array_equal(host(a), want)
+    np.testing.assert_array_equal(host(ho), X / 2)   # r = z = 1/2, n = 0
+    da = rng.integers(-2, 3, (n, H)).astype(np.float64)
+    dX = dev(rng.integers(-3, 4, (n, H)).astype(np.float64))
+    dX0 = host(dX)
+    dM = torch.full((E, n + 3, H), float("nan"), device="cuda", dtype=torch_dt(dt))
+    capi.ggnn_banded_step_bits_bwd(dt, n, B, H, E, tbt, dev(da.T, dt), Wt_, dX, dX, dM, n + 3)
+    wM = O.aggregate_transpose(n, s, d, e, da, E)
+    np.testing.assert_array_equal(host(dM[:, :n]), wM)
+    np.testing.assert_array_equal(host(dX), dX0 + np.einsum("eno,eho->nh", wM, W))
+
+
+# fp32: up to 512 row tiles of 32 nodes a workgroup holds one of them and eight type groups, above that several
+# rows and two groups (n = 16,640 and 16,896); fewer types than groups, one type.
+@pytest.mark.parametrize("B,H,E,nb,bias", [
+    (32, 32, 3, 520, True), (64, 64, 2, 260, False), (128, 64, 5, 130, True), (256, 32, 1, 65, False),
+    (512, 64, 3, 33, True), (128, 128, 9, 2, True), (256, 256, 2, 1, False), (512, 128, 1, 2, True),
+    (32, 256, 10, 3, True), (64, 256, 2, 5, True)])
+def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
+    say(f"f32 step form B={B} H={H} E={E} nb={nb} bias={bias}")
+    _step_case("f32", B, H, E, nb, B + H + E, bias)
+
+
+@pytest.mark.parametrize("B", [32, 128, 512])
+def test_f32_step_keeps_every_bit(B):
+    """One message per node through W = I: the aggregate is the sender's state, bit for bit, over the whole
+    range of float32 (the states are staged as three bf16 parts; the smallest part of 2^-90 is above the
+    subnormal range)."""
+    n, H = 2 * B, 32
+    rng = np.random.default_rng(B)
+    m = rng.integers(1 << 23, 1 << 24, (n, H)).astype(np.float64) * rng.choice([-1.0, 1.0], (n, H))
+    X = m * np.exp2(rng.integers(-90, 127, (n, H)) - 23.0)
+    src, dst = np.arange(n), (np.arange(n) + 1) % n
+    keep = np.abs(src // B - dst // B) <= 1
+    src, dst = src[keep], dst[keep]
+    bits, bits_t, _, _, _ = capi.ggnn_banded_pack_bits(n, 1, B, src, dst, np.zeros(len(src), int))
+    I = dev(np.eye(H)[None])
+    a = torch.full((n, H), float("nan"), device="cuda")
+    capi.ggnn_banded_step_bits("f32", n, B, H, 1, torch.from_numpy(bits).cuda(), dev(X), I, None, a)
+    want = np.zeros((n, H))
+    want[dst] = X[src]
+    np.testing.assert_array_equal(host(a), want)
+    dM, dX = torch.empty((1, n, H), device="cuda"), torch.empty((n, H), device="cuda")
+    capi.ggnn_banded_step_bits_bwd("f32", n, B, H, 1, torch.from_numpy(bits_t).cuda(), dev(X.T), I, None, dX, dM, n)
+    want = np.zeros((n, H))
+    want[src] = X[dst]
+    np.testing.assert_array_equal(host(dM[0]), want)
+    np.testing.assert_array_equal(host(dX), want)
