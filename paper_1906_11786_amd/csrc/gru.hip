@@ -36,17 +36,18 @@ __device__ __forceinline__ void stage_wT(S* dst, const S* src, int col0, int tid
 }
 
 // ---------------------------------------------------------------------------
-// Forward.  Workgroup: 16*WAVES nodes, wave w: 16 nodes (lane % 16), all
+// Forward in fp32.  Workgroup: 16*WAVES nodes, wave w: 16 nodes (lane % 16), all
 // features.  D[feature][node]: A operand = weight^T rows from LDS, B operand
 // = a / h / r*h fragments held in registers.  Phase A computes the reset
 // gate for all features (needed in full by (r*h) U_n), phase B the update
 // gate, the candidate and the new state, 32 features at a time.
 // ---------------------------------------------------------------------------
-template <typename S, int H, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __restrict__ a, const S* __restrict__ h,
-                                                                 const S* __restrict__ Wi, const S* __restrict__ U,
-                                                                 const float* __restrict__ b, S* __restrict__ h_out,
-                                                                 S* __restrict__ saved, int n_pad) {
+template <int H, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __restrict__ a, const float* __restrict__ h,
+                                                                 const float* __restrict__ Wi, const float* __restrict__ U,
+                                                                 const float* __restrict__ b, float* __restrict__ h_out,
+                                                                 float* __restrict__ saved, int n_pad) {
+  using S = float;
   constexpr int NT = WAVES * kWave;
   constexpr int V = 16 / sizeof(S);
   constexpr int PW = H + V;
@@ -59,22 +60,15 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __r
   const bool valid = n0 < n_pad;
   const int node = n0 + q;
 
-  // a is fp32; in bf16 mode it enters the matrix cores as hi + lo parts
-  // (al holds the lo part), so a Wi keeps fp32-level accuracy.
-  constexpr int NP = sizeof(S) == 2 ? 2 : 1;
-  frag_t<S> af[NP][KS], hf[KS], rh[KS];
+  frag_t<S> af[KS], hf[KS], rh[KS];
   if (valid) {
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       const float* row = a + (size_t)node * H;
       f32x4 x = *reinterpret_cast<const f32x4*>(row + 32 * kk + 4 * g);
       f32x4 y = *reinterpret_cast<const f32x4*>(row + 32 * kk + 16 + 4 * g);
-      float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-      if constexpr (NP == 2) {
-        split8(v, af[0][kk], af[NP - 1][kk]);
-      } else {
-        af[0][kk] = pack8<S>(v);
-      }
+      const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+      af[kk] = pack8<S>(v);
       hf[kk] = rowfrag<S>(h + (size_t)node * H, kk, g);
     }
   }
@@ -94,9 +88,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __r
     for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const frag_t<S> w0 = afrag(wt[0], p, kk);
-#pragma unroll
-        for (int part = 0; part < NP; ++part) mma(acc[p], w0, af[part][kk]);
+        mma(acc[p], afrag(wt[0], p, kk), af[kk]);
         mma(acc[p], afrag(wt[1], p, kk), hf[kk]);
       }
     float rhv[8];
@@ -128,12 +120,8 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __r
     for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const frag_t<S> w0 = afrag(wt[0], p, kk), w2 = afrag(wt[2], p, kk);
-#pragma unroll
-        for (int part = 0; part < NP; ++part) {
-          mma(az[p], w0, af[part][kk]);
-          mma(an[p], w2, af[part][kk]);
-        }
+        mma(az[p], afrag(wt[0], p, kk), af[kk]);
+        mma(an[p], afrag(wt[2], p, kk), af[kk]);
         mma(az[p], afrag(wt[1], p, kk), hf[kk]);
         mma(an[p], afrag(wt[3], p, kk), rh[kk]);
       }
@@ -232,17 +220,13 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_bwd_kernel(const float* __r
 }
 
 // ---------------------------------------------------------------------------
-// Weight staging of the large-H kernels.  Both stream Wi and U through LDS in
-// stages kept in fragment order; a staging unit is one lane vector (eight
-// elements, 16 bytes) of one fragment, and unit `lin` of a stage lands at
-// element 8 lin of the stage buffer.  The units are gathered from the
-// row-major weights, or copied from a packed array that holds every stage's
-// units back to back (GruPack), which turns staging into contiguous 16-byte
-// loads.
-//   forward stage s < NC:  16 columns 16s.. of gate r, blocks {Wi, U};
-//   forward stage s >= NC: 16 columns of gates z and n, {Wi_z, U_z, Wi_n, U_n};
-//     block unit (kk, lane (qq, gg)): column qq of the tile at input rows
-//     32kk + 4gg + {0..3}, 32kk + 16 + 4gg + {0..3};
+// Packed weights of the large-H kernels (H >= 128): lane vectors of eight
+// elements (16 bytes) back to back in the order the kernels read them.
+//   forward: fragment (feature group fw, matrix c of Wi_r, U_r, Wi_z, U_z,
+//     Wi_n, U_n, k step kk, tile i), lane (qq, gg): gate column
+//     32 fw + 2 qq + i at input rows 32 kk + 8 gg + {0..7};
+//   the reverse streams Wi and U through LDS in stages, unit `lin` of a stage
+//   landing at element 8 lin of the stage buffer:
 //   reverse pass 1, block m: U rows 16m.., gate n, fragments kk;
 //   reverse pass 2, block m: Wi rows 16m.., gates r, z, n, then U gates r, z;
 //     unit (gate, kk, lane (qq, gg)): row 16m + qq at gate columns
@@ -252,33 +236,23 @@ template <int H>
 struct GruPack {
   static constexpr int KS = H / 32, NC = H / 16, FRU = KS * 64;   // units per 16-wide block
   static constexpr int UNITS = 6 * NC * FRU;                      // units per region (6 H^2 / 8)
-  // first unit of forward stage s / reverse block m of pass p
-  __host__ __device__ static constexpr int fwd_stage(int s) {
-    return s < NC ? 2 * s * FRU : 2 * NC * FRU + 4 * (s - NC) * FRU;
-  }
+  // first unit of reverse block m of pass p
   __host__ __device__ static constexpr int rev_stage(int p, int m) {
     return p == 1 ? m * FRU : NC * FRU + 5 * m * FRU;
   }
 };
 
 template <typename S, int H>
-__device__ __forceinline__ u32x4 gru_fwd_unit(const S* __restrict__ Wi, const S* __restrict__ U, int s, int lin) {
-  constexpr int NC = H / 16, UPB = GruPack<H>::FRU;
-  const int blk = lin / UPB, rem = lin % UPB;
-  const int kk = rem / 64, l = rem % 64, qq = l % 16, gg = l / 16;
-  const int t16 = s < NC ? s : s - NC;
-  const int gate = s < NC ? 0 : 1 + blk / 2;
-  const S* src = ((blk % 2) ? U : Wi) + gate * H + 16 * t16 + qq;
-  const int r0 = 32 * kk + 4 * gg;
-  uint32_t w[4];
+__device__ __forceinline__ u32x4 gru_fwd_unit(const S* __restrict__ Wi, const S* __restrict__ U, int u) {
+  constexpr int KS = H / 32;
+  const int l = u % 64, i = (u / 64) % 2, kk = (u / 128) % KS, c = (u / (128 * KS)) % 6, fw = u / (128 * KS * 6);
+  const S* src = (c % 2 ? U : Wi) + (size_t)(32 * kk + 8 * (l / 16)) * 3 * H + (c / 2) * H + 32 * fw + 2 * (l % 16) + i;
+  u32x4 w;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    w[j] = static_cast<uint32_t>(src[(size_t)(r0 + 2 * j) * 3 * H]) |
-           (static_cast<uint32_t>(src[(size_t)(r0 + 2 * j + 1) * 3 * H]) << 16);
-    w[2 + j] = static_cast<uint32_t>(src[(size_t)(r0 + 16 + 2 * j) * 3 * H]) |
-               (static_cast<uint32_t>(src[(size_t)(r0 + 16 + 2 * j + 1) * 3 * H]) << 16);
-  }
-  return u32x4{w[0], w[1], w[2], w[3]};
+  for (int d = 0; d < 4; ++d)
+    w[d] = static_cast<uint32_t>(src[(size_t)(2 * d) * 3 * H]) |
+           (static_cast<uint32_t>(src[(size_t)(2 * d + 1) * 3 * H]) << 16);
+  return w;
 }
 
 template <typename S, int H>
@@ -316,16 +290,7 @@ __global__ __launch_bounds__(256) void gru_pack_kernel(const S* __restrict__ Wi,
   if (u >= 2 * P::UNITS) return;
   u32x4 v;
   if (u < P::UNITS) {
-    int s, lin;
-    if (u < 2 * P::NC * P::FRU) {
-      s = u / (2 * P::FRU);
-      lin = u % (2 * P::FRU);
-    } else {
-      const int x = u - 2 * P::NC * P::FRU;
-      s = P::NC + x / (4 * P::FRU);
-      lin = x % (4 * P::FRU);
-    }
-    v = gru_fwd_unit<S, H>(Wi, U, s, lin);
+    v = gru_fwd_unit<S, H>(Wi, U, u);
   } else {
     const int x = u - P::UNITS;
     int pass, m, lin;
@@ -346,140 +311,199 @@ __global__ __launch_bounds__(256) void gru_pack_kernel(const S* __restrict__ Wi,
 
 
 // ---------------------------------------------------------------------------
-// Forward for large H (bf16, H >= 128), the arithmetic of gru_fwd_kernel
-// with the weights shared through LDS: a workgroup of 8 waves (16 nodes
-// each) streams Wi and U once per 128 nodes in stages of one 16-column gate
-// tile, kept in fragment order, two stages per barrier and double buffered.
-// Pass 1 (tiles of the r gate) forms r and keeps r*h as operand fragments;
-// pass 2 (tiles of z and n) finishes the state.
+// Forward in bf16, one wave per 32 state features: a workgroup of H / 32 x NW
+// waves holds 16 NTL NW nodes, wave (fw, nw) the three gates' columns of
+// features 32 fw .. 32 fw + 31 for the 16 NTL nodes of group nw.  A wave per
+// 16 nodes instead (all features, the weights staged in LDS) reads every
+// weight from LDS for one or two products and gathers unpacked weights in
+// 2-byte pieces.  Here the nodes' operands (a as hi + lo, h, later r*h) sit in
+// LDS in fragment order, read by the H / 32 feature waves, and a wave's
+// weights come straight from global memory (L2), read once per workgroup, one k step
+// ahead of use: a k step reads three fragments per 16 nodes for 16 products
+// (r, z and the a part of n together); r*h then adds its share of n in a
+// second, short loop.  Measured: 131,040 nodes at H = 256, unpacked weights,
+// 322 -> 250 us per launch (packed, 262,144 nodes: 433 -> 410), 65,536 nodes
+// at H = 128 46 -> 36 us, 100,096 nodes at H = 64 35 -> 26 us; 2,048 nodes at
+// H = 256 58 -> 15 us.  Bound by the phases of a workgroup (staging, products,
+// nonlinearities), of which one runs at a time at H = 256, where the operands
+// take 131 KB of LDS.
+//
+// Feature order: the two 16-column tiles of a wave interleave, tile i, row m
+// is feature 2 m + i of the wave's 32, so that a weight dword (two consecutive
+// columns) holds an element of each tile, and a lane's accumulators of both
+// tiles are the eight consecutive features 8 g .. 8 g + 7 of its node: the
+// operands of the next product and 16-byte stores without lane exchanges.
+// k order: lane group g holds features 32 kk + 8 g + {0..7}.
 // ---------------------------------------------------------------------------
-template <typename S, int H, bool PK>
-__global__ __launch_bounds__(512) void gru_fwd_big_kernel(const float* __restrict__ a, const S* __restrict__ h,
-                                                          const S* __restrict__ Wi, const S* __restrict__ U,
-                                                          const S* __restrict__ pk, const float* __restrict__ b,
-                                                          S* __restrict__ h_out, S* __restrict__ saved, int n_pad) {
-  static_assert(sizeof(S) == 2, "bf16 only");
-  constexpr int NT = 512;
-  constexpr int KS = H / 32, NC = H / 16;
-  constexpr int FR = KS * 64 * 8;                  // elements of one (matrix, 16-column tile) block
-  // Stages are staged in pairs (one barrier per two stages; NC is even, so a
-  // pair never spans the two passes), double buffered: four stage buffers.
-  constexpr int SS = 2;
-  __shared__ __attribute__((aligned(16))) S lw[2 * SS][4 * FR];   // up to four blocks per stage
+// Buffer resource over `elems` 16-bit elements (loads through it take a
+// lane offset plus a uniform one, without 64-bit address arithmetic).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const bf16s* p, int elems) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16s*>(p), 0, elems * 2, 0x00027000);
+}
 
+template <int H, int NTL, int NW, bool PK>
+__global__ __launch_bounds__(H / 32 * NW * kWave) void gru_fwd_cols_kernel(
+    const float* __restrict__ a, const bf16s* __restrict__ h, const bf16s* __restrict__ Wi,
+    const bf16s* __restrict__ U, const bf16s* __restrict__ pk, const float* __restrict__ b,
+    bf16s* __restrict__ h_out, bf16s* __restrict__ saved, int n_pad) {
+  constexpr int KS = H / 32, FW = H / 32, TILES = NTL * NW;
+  __shared__ __attribute__((aligned(16))) bf16s fr[4][TILES][KS][kWave * 8];   // a hi, a lo, h, r*h
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int q = lane % 16, g = lane / 16;
-  const int n0 = xcd_swizzle(blockIdx.x, gridDim.x) * 128 + 16 * wave;
-  const bool valid = n0 < n_pad;
-  const int node = n0 + q;
+  const int fw = wave % FW, nw = wave / FW;
+  const int n0 = xcd_swizzle(blockIdx.x, gridDim.x) * 16 * TILES;
 
-  // Stage s of 2 NC: s < NC is pass 1, tile s (Wi, U columns of gate r);
-  // s >= NC is pass 2, tile s - NC (Wi, U columns of gates z and n); units
-  // as gru_fwd_unit, from the packed forward region when PK.
-  constexpr int UPB = KS * 64;                     // units per block
-  constexpr int RMAX = (4 * UPB + NT - 1) / NT;
-  u32x4 rr[SS][RMAX];
-  auto load_stage = [&](int s, int j) __attribute__((always_inline)) {
-    const int nblk = s < NC ? 2 : 4;
+  // Weights of k step kk, matrix c of (Wi_r, U_r, Wi_z, U_z, Wi_n, U_n): the two tiles' fragments from the packed
+  // copy, or eight dwords of gate columns 32 fw + 2 q, + 1 at input features 32 kk + 8 g + {0..7}.
+  const auto rp = buffer_of(PK ? pk : Wi, PK ? 12 * H * H : 6 * H * H);
+  const auto ru = buffer_of(U, 6 * H * H);
+  const int woff = PK ? fw * 6 * KS * 2048 + lane * 16 : (8 * g * 3 * H + 32 * fw + 2 * q) * 2;
+  auto load_w = [&](int c, int kk, uint32_t (&w)[8]) __attribute__((always_inline)) {
+    if constexpr (PK) {
 #pragma unroll
-    for (int u = 0; u < RMAX; ++u) {
-      const int lin = u * NT + tid;
-      if (lin < nblk * UPB) {
-        if constexpr (PK)
-          rr[j][u] = *reinterpret_cast<const u32x4*>(pk + ((size_t)GruPack<H>::fwd_stage(s) + lin) * 8);
-        else
-          rr[j][u] = gru_fwd_unit<S, H>(Wi, U, s, lin);
+      for (int i = 0; i < 2; ++i) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rp, woff, ((c * KS + kk) * 2 + i) * 1024, 0);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) w[4 * i + d] = v[d];
       }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        w[e] = __builtin_amdgcn_raw_buffer_load_b32(c % 2 ? ru : rp, woff, ((32 * kk + e) * 3 * H + (c / 2) * H) * 2, 0);
     }
   };
-  auto store_stage = [&](int s, int j, int bf) __attribute__((always_inline)) {
-    const int nblk = s < NC ? 2 : 4;
+  auto frag = [&](const uint32_t (&w)[8], int i) __attribute__((always_inline)) {
+    u32x4 v;
 #pragma unroll
-    for (int u = 0; u < RMAX; ++u) {
-      const int lin = u * NT + tid;
-      if (lin < nblk * UPB) *reinterpret_cast<u32x4*>(&lw[bf][lin * 8]) = rr[j][u];
-    }
+    for (int d = 0; d < 4; ++d)
+      v[d] = PK ? w[4 * i + d] : __builtin_amdgcn_perm(w[2 * d + 1], w[2 * d], i ? 0x07060302u : 0x05040100u);
+    return __builtin_bit_cast(bf16x8, v);
   };
 
-  // Operand fragments of the 16 nodes (accumulator-compatible k order):
-  // a as hi + lo, h, and later r*h.
-  frag_t<S> af[2][KS], hf[KS], rh[KS];
-  if (valid) {
+  auto state8 = [&](int t, float (&v)[8]) __attribute__((always_inline)) {
+    const u32x4 s8 = *reinterpret_cast<const u32x4*>(&fr[2][nw * NTL + t][fw][lane * 8]);
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const float* row = a + (size_t)node * H;
-      const f32x4 x = *reinterpret_cast<const f32x4*>(row + 32 * kk + 4 * g);
-      const f32x4 y = *reinterpret_cast<const f32x4*>(row + 32 * kk + 16 + 4 * g);
-      const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-      split8(v, af[0][kk], af[1][kk]);
-      hf[kk] = rowfrag<S>(h + (size_t)node * H, kk, g);
+    for (int d = 0; d < 4; ++d) v[2 * d] = lo_f(s8[d]), v[2 * d + 1] = hi_f(s8[d]);
+  };
+  auto frag_of = [&](int arr, int t, int kk) __attribute__((always_inline)) {
+    return load8(&fr[arr][nw * NTL + t][kk][lane * 8]);
+  };
+
+  // Operand fragments of the nodes, NTL per wave: unit u = node tile u / KS, k step u % KS (a tile past the end
+  // repeats the last one; its results are not stored).
+  {
+    f32x4 x[NTL], y[NTL];
+    u32x4 hv[NTL];
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) {
+      const int u = wave * NTL + j, tile = min(n0 + 16 * (u / KS), n_pad - 16);
+      const size_t at = (size_t)(tile + q) * H + 32 * (u % KS) + 8 * g;
+      x[j] = *reinterpret_cast<const f32x4*>(a + at);
+      y[j] = *reinterpret_cast<const f32x4*>(a + at + 4);
+      hv[j] = *reinterpret_cast<const u32x4*>(h + at);
+    }
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) {
+      const int u = wave * NTL + j, t = u / KS, kk = u % KS;
+      const float v[8] = {x[j][0], x[j][1], x[j][2], x[j][3], y[j][0], y[j][1], y[j][2], y[j][3]};
+      bf16x8 hi, lo;
+      split8(v, hi, lo);
+      *reinterpret_cast<bf16x8*>(&fr[0][t][kk][lane * 8]) = hi;
+      *reinterpret_cast<bf16x8*>(&fr[1][t][kk][lane * 8]) = lo;
+      *reinterpret_cast<u32x4*>(&fr[2][t][kk][lane * 8]) = hv[j];
     }
   }
-  float rhv[8];
-  static_assert(NC % SS == 0, "stage pairs must not span the two passes");
+  uint32_t w[2][5][8], un[2][8];   // of a k step: Wi_r, U_r, Wi_z, U_z, Wi_n; U_n
 #pragma unroll
-  for (int j = 0; j < SS; ++j) load_stage(j, j);
-  auto compute = [&](int s, const S* L) __attribute__((always_inline)) {
-    if (s < NC) {
-      f32x4 ar = {0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < 5; ++c) load_w(c, 0, w[0][c]);
+
+  // The lane's eight features: 32 fw + 8 g + e, e = 2 j + i (tile i, accumulator element j).  The sums start from
+  // the bias.
+  const int fe = 32 * fw + 8 * g;
+  f32x4 acc[3][2][NTL];
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const frag_t<S> w0 = load_fragi<S>(L, kk, lane);
-        mma(ar, w0, af[0][kk]);
-        mma(ar, w0, af[1][kk]);
-        mma(ar, load_fragi<S>(L + FR, kk, lane), hf[kk]);
-      }
-      const int f = 16 * s + 4 * g;
-      float r[4];
+  for (int c = 0; c < 3; ++c) {
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(b + c * H + fe),
+                hi = *reinterpret_cast<const f32x4*>(b + c * H + fe + 4);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        r[j] = sigmoidf_(ar[j] + b[f + j]);
-        rhv[4 * (s % 2) + j] = r[j] * static_cast<float>(hf[s / 2][4 * (s % 2) + j]);
-      }
-      if (saved) store4(saved + (size_t)node * 3 * H + f, r[0], r[1], r[2], r[3]);
-      if (s % 2 == 1) rh[s / 2] = pack8<S>(rhv);
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) acc[c][i][t] = f32x4{lo[i], lo[2 + i], hi[i], hi[2 + i]};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    if (kk + 1 < KS) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) load_w(c, kk + 1, w[(kk + 1) & 1][c]);
     } else {
-      const int t16 = s - NC;
-      f32x4 az = {0.f, 0.f, 0.f, 0.f}, an = {0.f, 0.f, 0.f, 0.f};
+      load_w(5, 0, un[0]);
+    }
+    bf16x8 f[5][2];
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const frag_t<S> wz = load_fragi<S>(L, kk, lane), wn = load_fragi<S>(L + 2 * FR, kk, lane);
-        mma(az, wz, af[0][kk]);
-        mma(az, wz, af[1][kk]);
-        mma(an, wn, af[0][kk]);
-        mma(an, wn, af[1][kk]);
-        mma(az, load_fragi<S>(L + FR, kk, lane), hf[kk]);
-        mma(an, load_fragi<S>(L + 3 * FR, kk, lane), rh[kk]);
-      }
-      const int f = 16 * t16 + 4 * g;
-      float z[4], nn[4], o[4];
+    for (int c = 0; c < 5; ++c)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        z[j] = sigmoidf_(az[j] + b[H + f + j]);
-        nn[j] = tanhf_(an[j] + b[2 * H + f + j]);
-        const float hv = static_cast<float>(hf[t16 / 2][4 * (t16 % 2) + j]);
-        o[j] = z[j] * hv + (1.f - z[j]) * nn[j];
-      }
-      store4(h_out + (size_t)node * H + f, o[0], o[1], o[2], o[3]);
-      if (saved) {
-        store4(saved + (size_t)node * 3 * H + H + f, z[0], z[1], z[2], z[3]);
-        store4(saved + (size_t)node * 3 * H + 2 * H + f, nn[0], nn[1], nn[2], nn[3]);
+      for (int i = 0; i < 2; ++i) f[c][i] = frag(w[kk & 1][c], i);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      const bf16x8 ah = frag_of(0, t, kk), al = frag_of(1, t, kk), hf = frag_of(2, t, kk);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        mma(acc[0][i][t], f[0][i], ah);
+        mma(acc[1][i][t], f[2][i], ah);
+        mma(acc[2][i][t], f[4][i], ah);
+        mma(acc[0][i][t], f[0][i], al);
+        mma(acc[1][i][t], f[2][i], al);
+        mma(acc[2][i][t], f[4][i], al);
+        mma(acc[0][i][t], f[1][i], hf);
+        mma(acc[1][i][t], f[3][i], hf);
       }
     }
-  };
+  }
 #pragma unroll
-  for (int s0 = 0; s0 < 2 * NC; s0 += SS) {
-    const int bf = ((s0 / SS) & 1) * SS;
+  for (int t = 0; t < NTL; ++t) {
+    const int tile = n0 + 16 * (nw * NTL + t);
+    float hs[8], r[8], rh[8];
+    state8(t, hs);
 #pragma unroll
-    for (int j = 0; j < SS; ++j) store_stage(s0 + j, j, bf + j);
-    __syncthreads();
-    if (s0 + SS < 2 * NC) {
-#pragma unroll
-      for (int j = 0; j < SS; ++j) load_stage(s0 + SS + j, j);
+    for (int e = 0; e < 8; ++e) {
+      r[e] = sigmoidf_(acc[0][e & 1][t][e >> 1]);
+      rh[e] = r[e] * hs[e];
     }
-    if (!valid) continue;
+    *reinterpret_cast<bf16x8*>(&fr[3][nw * NTL + t][fw][lane * 8]) = pack8<bf16s>(rh);
+    if (saved && tile < n_pad)
+      *reinterpret_cast<bf16x8*>(saved + (size_t)(tile + q) * 3 * H + fe) = pack8<bf16s>(r);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int j = 0; j < SS; ++j) compute(s0 + j, lw[bf + j]);
+  for (int kk = 0; kk < KS; ++kk) {
+    if (kk + 1 < KS) load_w(5, kk + 1, un[(kk + 1) & 1]);
+    const bf16x8 f0 = frag(un[kk & 1], 0), f1 = frag(un[kk & 1], 1);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      const bf16x8 rh = frag_of(3, t, kk);
+      mma(acc[2][0][t], f0, rh);
+      mma(acc[2][1][t], f1, rh);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NTL; ++t) {
+    const int tile = n0 + 16 * (nw * NTL + t);
+    if (tile >= n_pad) continue;
+    float hs[8], z[8], n[8], o[8];
+    state8(t, hs);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      z[e] = sigmoidf_(acc[1][e & 1][t][e >> 1]);
+      n[e] = tanhf_(acc[2][e & 1][t][e >> 1]);
+      o[e] = __builtin_fmaf(z[e], hs[e] - n[e], n[e]);   // z h + (1 - z) n
+    }
+    const size_t node = tile + q;
+    *reinterpret_cast<bf16x8*>(h_out + node * H + fe) = pack8<bf16s>(o);
+    if (saved) {
+      *reinterpret_cast<bf16x8*>(saved + node * 3 * H + H + fe) = pack8<bf16s>(z);
+      *reinterpret_cast<bf16x8*>(saved + node * 3 * H + 2 * H + fe) = pack8<bf16s>(n);
+    }
   }
 }
 
@@ -927,24 +951,38 @@ hipError_t gru_pack_h(const void* Wi, const void* U, void* packed, hipStream_t s
 template <typename S, int H>
 hipError_t gru_fwd_h(int n_pad, const float* a, const void* h, const void* Wi, const void* U, const float* b,
                      void* h_out, void* saved, const void* packed, hipStream_t st) {
-  if constexpr (gru_big<S, H>()) {
-    const S* pk = static_cast<const S*>(packed);
-#define GGNN_GRU_FWD_BIG(PK)                                                                                   \
-  hipLaunchKernelGGL((dev::gru_fwd_big_kernel<S, H, PK>), dim3((n_pad + 127) / 128), dim3(512), 0, st, a,      \
-                     static_cast<const S*>(h), static_cast<const S*>(Wi), static_cast<const S*>(U), pk, b,      \
-                     static_cast<S*>(h_out), static_cast<S*>(saved), n_pad)
-    if (pk != nullptr)
-      GGNN_GRU_FWD_BIG(true);
-    else
-      GGNN_GRU_FWD_BIG(false);
-#undef GGNN_GRU_FWD_BIG
+  if constexpr (sizeof(S) == 2) {
+    const S* pk = gru_big<S, H>() ? static_cast<const S*>(packed) : nullptr;
+    constexpr int NW = H >= 128 ? 1 : 128 / H;
+#define GGNN_GRU_COLS(NTL, PK)                                                                                 \
+  hipLaunchKernelGGL((dev::gru_fwd_cols_kernel<H, NTL, NW, PK>), dim3((n_pad + 16 * NTL * NW - 1) / (16 * NTL * NW)), \
+                     dim3(H / 32 * NW * 64), 0, st, a, static_cast<const S*>(h), static_cast<const S*>(Wi),     \
+                     static_cast<const S*>(U), pk, b, static_cast<S*>(h_out), static_cast<S*>(saved), n_pad)
+    // 16 nodes per workgroup while that leaves no compute unit two of them (2,048 nodes at H = 256: 15.0 us
+    // against 23.8 with 64, at H = 128: 7.8 against 9.7), else 64, so that the weights are read less often
+    // (12,352 nodes: 27 us against 52 with 16 and 36 with 32; H = 128: 12.7 / 16.7 / 13.0).
+    const bool small = H >= 128 && n_pad <= 4096;
+    if constexpr (gru_big<S, H>()) {
+      if (small && pk != nullptr)
+        GGNN_GRU_COLS(1, true);
+      else if (small)
+        GGNN_GRU_COLS(1, false);
+      else if (pk != nullptr)
+        GGNN_GRU_COLS(4, true);
+      else
+        GGNN_GRU_COLS(4, false);
+    } else {
+      GGNN_GRU_COLS(4, false);
+    }
+#undef GGNN_GRU_COLS
+    return hipGetLastError();
+  } else {
+    constexpr int WAVES = 4;
+    hipLaunchKernelGGL((dev::gru_fwd_kernel<H, WAVES>), dim3((n_pad + 16 * WAVES - 1) / (16 * WAVES)),
+                       dim3(WAVES * 64), 0, st, a, static_cast<const float*>(h), static_cast<const float*>(Wi),
+                       static_cast<const float*>(U), b, static_cast<float*>(h_out), static_cast<float*>(saved), n_pad);
     return hipGetLastError();
   }
-  constexpr int WAVES = 4;
-  hipLaunchKernelGGL((dev::gru_fwd_kernel<S, H, WAVES>), dim3((n_pad + 16 * WAVES - 1) / (16 * WAVES)),
-                     dim3(WAVES * 64), 0, st, a, static_cast<const S*>(h), static_cast<const S*>(Wi),
-                     static_cast<const S*>(U), b, static_cast<S*>(h_out), static_cast<S*>(saved), n_pad);
-  return hipGetLastError();
 }
 
 template <typename S, int H>

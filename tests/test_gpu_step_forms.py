@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_helpers import say, dev, host, torch_dt
+from gpu_helpers import say, dev, host, round_to, torch_dt
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +97,32 @@ def test_f32_step_keeps_every_bit(B):
     want[src] = X[dst]
     np.testing.assert_array_equal(host(dM[0]), want)
     np.testing.assert_array_equal(host(dX), want)
+
+
+# bf16 node update: 16 nodes per workgroup up to 4,096 nodes at H >= 128, else 64 (128 at H = 64, 256 at H = 32),
+# the last workgroup partly or mostly past the end.
+@pytest.mark.parametrize("H,n", [(32, 32), (32, 288), (64, 160), (64, 4128), (128, 32), (128, 4096), (128, 4128),
+                                 (256, 96), (256, 4096), (256, 4160)])
+def test_gru_update_forms(H, n):
+    say(f"gru_update form H={H} n={n}")
+    rng = np.random.default_rng(H + n)
+    k = 1 / np.sqrt(H)
+    a = round_to("f32", 3 * rng.standard_normal((n, H)))
+    h = round_to("bf16", rng.standard_normal((n, H)))
+    Wi, U = (round_to("bf16", rng.uniform(-k, k, (H, 3 * H))) for _ in range(2))
+    b = round_to("f32", rng.uniform(-k, k, 3 * H))
+    out = torch.full((n, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    sv = torch.full((n, 3 * H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    args = ("bf16", n, H, dev(a), dev(h, "bf16"), dev(Wi, "bf16"), dev(U, "bf16"), dev(b))
+    capi.ggnn_gru_update(*args, out, sv)
+    y, r, z, nn = O.gru_forward(a, h, Wi, U, b)
+    # Stored in bf16: half a unit in the last of 8 bits, at most 2^-8 of the value.  Before that r*h (|r*h| < 5) is
+    # rounded to bf16, an error of at most 2^-8 |r h| in each of H terms times |U| <= H^-1/2: independent, about
+    # 2^-8 rms(r h) / 3 in the candidate, six times which bounds the largest of 10^6 (the other operands are exact
+    # or split to 16 bits, 2^-17).
+    slack = 6 * 2.0 ** -8 * np.sqrt(np.mean((r * h) ** 2)) / 3
+    for got, want in ((out, y), (sv, np.concatenate([r, z, nn], 1))):
+        assert np.max(np.abs(host(got) - want) - 2.0 ** -8 * np.abs(want)) <= slack
+    ns = torch.full((n, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    capi.ggnn_gru_update(*args, ns, None)
+    assert torch.equal(ns, out)
