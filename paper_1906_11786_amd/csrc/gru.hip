@@ -1098,7 +1098,9 @@ hipError_t launch_gru_bwd(int dt, int n_pad, int H, const float* dh_out, const f
   void* part = static_cast<char*>(ws) + ghat_bytes(dt, n_pad, H);
   hipError_t err = launch_gru_bwd_nodes(dt, n_pad, H, dh_out, h, saved, Wi, U, da, dh, ghat, st);
   if (err != hipSuccess) return err;
-  return launch_gru_wgrad(dt, n_pad, H, a, h, saved, ghat, dWi, dU, db, part, st);
+  ReduceList red;   // the partial sums of dWi, dU and db in one launch
+  err = launch_gru_wgrad(dt, n_pad, H, a, h, saved, ghat, dWi, dU, db, part, st, &red);
+  return err == hipSuccess ? launch_reduce_multi(red, st) : err;
 }
 #endif
 
