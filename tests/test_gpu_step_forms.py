@@ -126,3 +126,25 @@ def test_gru_update_forms(H, n):
     ns = torch.full((n, H), float("nan"), device="cuda", dtype=torch.bfloat16)
     capi.ggnn_gru_update(*args, ns, None)
     assert torch.equal(ns, out)
+
+
+# Sparse step: from 1,024 groups of 16 receivers on, all types' weights in LDS where they fit (E <= 14 at H = 64 in
+# bf16); uneven shares of the groups, a receiver with more senders than the LDS copy of its group holds, odd E.
+@pytest.mark.parametrize("dt,H,E,n", [("bf16", 64, 14, 16384), ("bf16", 64, 15, 16384), ("bf16", 64, 1, 16352),
+                                      ("bf16", 32, 7, 20000), ("f32", 32, 11, 16416), ("f32", 64, 3, 16416)])
+def test_sparse_step_forms_integer_exact(dt, H, E, n):
+    say(f"sparse_step form dt={dt} H={H} E={E} n={n}")
+    rng = np.random.default_rng(H + E + n)
+    m = 4 * n
+    src, dst, et = rng.integers(0, n, m), rng.integers(0, n, m), rng.integers(0, E, m)
+    dst[:600], et[:600] = n - 5, E - 1          # 600 senders of one receiver
+    dst[600:700], et[600:700] = 17, 0
+    X = rng.integers(-2, 3, (n, H)).astype(np.float64)
+    W = rng.integers(-1, 2, (E, H, H)).astype(np.float64)
+    bias = rng.integers(-2, 3, (E, H)).astype(np.float64) if E % 2 else None
+    row_ptr, col, _ = capi.ggnn_sparse_csr(n, E, src, dst, et)
+    a = torch.full((n, H), float("nan"), device="cuda")
+    capi.ggnn_sparse_step(dt, n, H, E, torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), len(col),
+                          dev(X, dt), dev(W.transpose(0, 2, 1), dt), None if bias is None else dev(bias), a)
+    s, d, e, _ = O.dedupe_edges(src, dst, et)
+    np.testing.assert_array_equal(host(a), O.aggregate(n, s, d, e, O.msg_transform(X, W, bias)))
