@@ -1,10 +1,11 @@
-// Fused step on a 1-bit block band for float32 states (every H and B), the
-// products of the fused step of Eq. 3 in the operand order of Algorithm 1:
+// Step on a 1-bit block band with the weights read straight from global memory: float32 (every size) and the bf16
+// sizes that the other step kernels serve badly (small grids at H >= 128, blocks that do not fit in LDS whole at
+// H <= 64), the products of the fused step of Eq. 3 in the operand order of Algorithm 1:
 //   forward:  a[k]    = sum_e (sum_s bits[e][k][s] X[k-1+s]) W_e   (+ deg_e b_e)
 //   reverse:  dM_e[k] = sum_s bits_t[e][k][s] da[k-1+s]            (stored)
 //             dX[k]   = dX_in[k] + sum_e dM_e[k] W_e^T
 //
-// What bounds the aggregation in fp32 is the matrix-core rate: an fp32 k step
+// fp32: what bounds the aggregation is the matrix-core rate: an fp32 k step
 // of 32 nodes takes eight v_mfma_f32_16x16x4_f32 of 32 cycles.  The band's
 // entries are 0 or 1, exact in bf16, so the states are split instead, once,
 // when they are staged: x = hi + mid + lo with bf16 parts (8 + 8 + 8
@@ -12,6 +13,13 @@
 // v_mfma_f32_16x16x32_bf16 of 16 cycles with float accumulation: the same
 // sums of the same values at 5.3 times the rate.  The transform by W_e stays
 // on the fp32 instructions: there both operands have 24 bits.
+//
+// bf16: the aggregate enters the transform as hi + lo (forward) or rounded as
+// stored (reverse), as in the other step kernels.  On small grids those are
+// bound by how few waves they start: the wide kernel shares every weight
+// between a block's rows through LDS, at the price of a barrier per 32 weight
+// rows and B / 32 waves per block.  Here a workgroup's waves take the
+// edge types side by side and add their sums once at the end.
 //
 // The transform's contraction over features is split into slices of HQ
 // features, (A_e X) W_e = sum_q (A_e X[:, q]) W_e[q, :]: per slice the three
@@ -23,16 +31,24 @@
 // 64-node chunks per type and multiplied them in fp32 (205 us per step launch
 // there); the distance from a 64-bit reference 1.6e-6 -> 1.3e-6 of the norm
 // (fewer roundings per sum).  Bound now by the transform's fp32 products.
+// bf16, 12,352 nodes, B = 64, H = 128, 7 types: 60 -> 28 us per forward and
+// 51 -> 25 us per reverse launch against the wide kernel, bound by the chain
+// of a wave's types (bit rows, products, weights).
 #include "device_common.h"
 #include "kernels.h"
 
 namespace ggnn {
 namespace dev {
 
-template <int H, int B, int WAVES, int TG>
-struct SplitCfg {
-  // Features per slice: as many as three parts of three blocks leave room for.
-  static constexpr int HQ = B >= 512 ? 16 : (B >= 128 || H == 32 || H == 256 ? 32 : 64);
+template <typename S, int H, int B, int WAVES, int TG>
+struct DirectCfg {
+  static constexpr bool F32 = sizeof(S) == 4;
+  static constexpr int PARTS = F32 ? 3 : 1;
+  // Features per slice: as many as the parts of three blocks (in LDS) and the
+  // slice's aggregate (in registers, next to the output sums) leave room for.
+  static constexpr int HQF = B >= 512 ? 16 : (B >= 128 || H == 32 || H == 256 ? 32 : 64);
+  static constexpr int HQB = B >= 512 || H == 32 ? 32 : (B >= 256 || H == 64 || H == 256 ? 64 : 128);
+  static constexpr int HQ = F32 ? HQF : HQB;
   static constexpr int NQ = H / HQ, MQ = HQ / 16, MT = H / 16;
   static constexpr int RPW = 32, NTW = 2;        // rows per wave, 16-row tiles per wave
   static constexpr int R = WAVES * RPW, NT = TG * WAVES * kWave;
@@ -45,8 +61,9 @@ struct SplitCfg {
   static constexpr int PLANE = 3 * B * HQ;       // elements of one part of the staged window
   // The groups' partial sums meet in LDS, one row tile at a time.
   static constexpr int RED = TG == 1 ? 0 : TG * WAVES * MT * 1024;
-  static constexpr int LDS = 3 * PLANE * 2 > RED ? 3 * PLANE * 2 : RED;
-  static constexpr int GM = MQ >= 4 || H == 256 ? 2 : 4;     // output tiles whose weights are loaded together
+  static constexpr int LDS = PARTS * PLANE * 2 > RED ? PARTS * PLANE * 2 : RED;
+  // Output tiles whose weights are loaded together.
+  static constexpr int GM = F32 ? (MQ >= 4 || H == 256 ? 2 : 4) : (HQ == 128 ? 2 : 4);
 };
 
 // x = hi + mid + lo, each with at most eight significant bits (the low words
@@ -70,7 +87,7 @@ __device__ __forceinline__ void split3x8(const float (&v)[8], u32x4 (&o)[3]) {
   }
 }
 
-__device__ __forceinline__ bf16x8 split_bits_frag(uint32_t byte) {   // bit i -> element i (0 or 1)
+__device__ __forceinline__ bf16x8 direct_bits_frag(uint32_t byte) {   // bit i -> element i (0 or 1)
   const uint32_t x = byte * 0x8001u;
   u32x4 w;
 #pragma unroll
@@ -78,7 +95,7 @@ __device__ __forceinline__ bf16x8 split_bits_frag(uint32_t byte) {   // bit i ->
   return __builtin_bit_cast(bf16x8, w);
 }
 
-template <int NB> struct SplitBits {
+template <int NB> struct DirectBits {
   static constexpr int NW = NB < 4 ? 1 : NB / 4;
   uint32_t w[NW];
   __device__ __forceinline__ void load(const uint8_t* p) {
@@ -110,18 +127,27 @@ template <int NB> struct SplitBits {
   }
 };
 
-__device__ __forceinline__ bool split_any(uint32_t x) { return __builtin_amdgcn_ballot_w64(x != 0u) != 0; }
+__device__ __forceinline__ bool direct_any(uint32_t x) { return __builtin_amdgcn_ballot_w64(x != 0u) != 0; }
+
+// Row of feature f of a 32-feature group in bf16: tile 2j + i of group j holds
+// features 32j + 8r + 4i + {0..3} in rows 4r + {0..3}, so that a lane's sums
+// of two tiles are eight consecutive features (a fragment of the transform,
+// weight rows read 16 bytes at a time, one 16-byte store of dM).
+__device__ __forceinline__ int direct_slot(int f) {
+  const int w = f % 32;
+  return 32 * (f / 32) + 16 * ((w % 8) / 4) + 4 * (w / 8) + w % 4;
+}
 
 // Workgroup: R = 32 WAVES rows of block row k, TG * WAVES waves; wave w takes
 // rows 32 (w % WAVES) .. + 31 and the edge types of group w / WAVES (a
 // contiguous range).  V = X (forward, [n_pad][H]) or da (reverse,
 // [H][n_pad]); W [E][H][H]; Wt = W_e^T or NULL (forward).
-template <int H, int B, int WAVES, int TG, bool REV>
-__global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
-    const uint8_t* __restrict__ bits, const float* __restrict__ V, const float* __restrict__ W,
-    const float* __restrict__ Wt, const float* __restrict__ bias, float* out, int n_pad, int E, const float* dX_in,
-    float* __restrict__ dM, long ldm) {
-  using C = SplitCfg<H, B, WAVES, TG>;
+template <typename S, int H, int B, int WAVES, int TG, bool REV>
+__global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
+    const uint8_t* __restrict__ bits, const S* __restrict__ V, const S* __restrict__ W, const S* __restrict__ Wt,
+    const float* __restrict__ bias, float* out, int n_pad, int E, const float* dX_in, S* __restrict__ dM, long ldm) {
+  using C = DirectCfg<S, H, B, WAVES, TG>;
+  constexpr bool F32 = C::F32;
   constexpr int NT = C::NT, HQ = C::HQ, NQ = C::NQ, MQ = C::MQ, MT = C::MT, NTW = C::NTW, RB = C::RB, GM = C::GM;
   constexpr int ROWB = B / 8, TPR = B / C::R;
   static_assert(C::LDS <= 160 * 1024, "LDS");
@@ -137,7 +163,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
   const int s_lo = (k == 0) ? 1 : 0, s_hi = (k == nb - 1) ? 1 : 2;
   const int e_lo = tg * E / TG, e_hi = (tg + 1) * E / TG;
 
-  auto load_bits = [&](int e, SplitBits<RB> (&dst)[3][NTW]) __attribute__((always_inline)) {
+  auto load_bits = [&](int e, DirectBits<RB> (&dst)[3][NTW]) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
       const uint8_t* p = bits + ((((size_t)e * nb + k) * 3 + s) * B + rw + q) * ROWB + g * RB;
@@ -152,24 +178,28 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
     }
   };
 
-  // One slice of the three blocks: a unit is eight nodes of four features
-  // (forward: eight 16-byte row loads) or of one feature (reverse).
+  // One slice of the three blocks, in fragment order.  fp32: a unit is eight
+  // nodes of four features (forward: eight 16-byte row loads) or of one
+  // feature (reverse), split into its parts.  bf16: an 8 x 8 tile transposed in registers (forward) or eight nodes of
+  // one feature (reverse).
+  auto at = [&](int s, int f, int c) __attribute__((always_inline)) {   // feature slot f, nodes c .. c + 7 of block s
+    const int kk = C::KCONT ? c / 32 : (c % (B / 4)) / 8, gg = C::KCONT ? (c / 8) % 4 : c / (B / 4);
+    return xs + s * B * HQ + fo<bf16s>(kk * MQ + f / 16, f % 16 + 16 * gg, 0);
+  };
   auto stage = [&](int qs) __attribute__((always_inline)) {
     auto put = [&](int s, int f, int c, const float (&v)[8]) __attribute__((always_inline)) {
-      const int kk = C::KCONT ? c / 32 : (c % (B / 4)) / 8, gg = C::KCONT ? (c / 8) % 4 : c / (B / 4);
       u32x4 o[3];
       split3x8(v, o);
-      bf16s* d = xs + s * B * HQ + fo<bf16s>(kk * MQ + f / 16, f % 16 + 16 * gg, 0);
 #pragma unroll
-      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(d + p * C::PLANE) = o[p];
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(at(s, f, c) + p * C::PLANE) = o[p];
     };
-    if constexpr (!REV) {
+    if constexpr (F32 && !REV) {
       constexpr int UB = (B / 8) * (HQ / 4);
       for (int u = tid; u < 3 * UB; u += NT) {
         const int s = u / UB, r = u % UB, f0 = 4 * (r % (HQ / 4)), c = 8 * (r / (HQ / 4));
         if (s < s_lo || s > s_hi) continue;
         f32x4 x[8];
-        const float* p = V + (size_t)((k - 1 + s) * B + c) * H + qs * HQ + f0;
+        const S* p = V + (size_t)((k - 1 + s) * B + c) * H + qs * HQ + f0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4*>(p + (size_t)i * H);
 #pragma unroll
@@ -178,15 +208,36 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
           put(s, f0 + j, c, v);
         }
       }
+    } else if constexpr (F32) {
+      constexpr int UB = (B / 8) * HQ;
+      for (int u = tid; u < 3 * UB; u += NT) {
+        const int s = u / UB, r = u % UB, f = 16 * (r / (16 * (B / 8))) + r % 16, c = 8 * ((r / 16) % (B / 8));
+        if (s < s_lo || s > s_hi) continue;
+        const S* p = V + (size_t)(qs * HQ + f) * n_pad + (k - 1 + s) * B + c;
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+        const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        put(s, f, c, v);
+      }
+    } else if constexpr (!REV) {
+      constexpr int UB = (B / 8) * (HQ / 8);
+      for (int u = tid; u < 3 * UB; u += NT) {
+        // eight neighbouring lanes take eight node octets of one feature octet: their LDS writes fall on
+        // different lane groups' pieces
+        const int s = u / UB, r = u % UB, c = 8 * (r % (B / 8)), f0 = 8 * (r / (B / 8));
+        if (s < s_lo || s > s_hi) continue;
+        u32x4 x[8];
+        tile_load<bf16s>(x, V + (size_t)((k - 1 + s) * B + c) * H + qs * HQ + f0, H);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          *reinterpret_cast<u32x4*>(at(s, direct_slot(f0 + j), c)) = tile_row_T<bf16s>(x, j);
+      }
     } else {
       constexpr int UB = (B / 8) * HQ;
       for (int u = tid; u < 3 * UB; u += NT) {
         const int s = u / UB, r = u % UB, f = 16 * (r / (16 * (B / 8))) + r % 16, c = 8 * ((r / 16) % (B / 8));
         if (s < s_lo || s > s_hi) continue;
-        const float* p = V + (size_t)(qs * HQ + f) * n_pad + (k - 1 + s) * B + c;
-        const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
-        const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-        put(s, f, c, v);
+        *reinterpret_cast<u32x4*>(at(s, direct_slot(f), c)) =
+            *reinterpret_cast<const u32x4*>(V + (size_t)(qs * HQ + f) * n_pad + (k - 1 + s) * B + c);
       }
     }
   };
@@ -198,31 +249,38 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
     for (int m = 0; m < MT; ++m) acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int qs = 0; qs < NQ; ++qs) {
-    SplitBits<RB> cur[3][NTW], nxt[3][NTW];
+    DirectBits<RB> cur[3][NTW], nxt[3][NTW];
     if (e_lo < e_hi) load_bits(e_lo, cur);
     if (qs > 0) __syncthreads();   // every wave is done with the previous slice
     stage(qs);
     __syncthreads();
     for (int e = e_lo; e < e_hi; ++e) {
       if (e + 1 < e_hi) load_bits(e + 1, nxt);
-      // Weight fragments of output tiles mo (A operand: row = output feature
-      // 16 mo + q, k = the slice's features 16 m + 4 g + {0..3}).
-      auto load_w = [&](int mo, f32x4 (&wf)[MQ]) __attribute__((always_inline)) {
-        const int f = qs * HQ + 4 * g, o = 16 * mo + q;
+      // Weight fragments of output tile mo (A operand: row = output feature
+      // 16 mo + q; fp32: k = the slice's features 16 m + 4 g + {0..3}, bf16:
+      // 32 kk + 8 g + {0..7}).
+      constexpr int GMT = GM < MT ? GM : MT, WF = F32 ? MQ : HQ / 32;   // tiles per load, 16-byte pieces per tile
+      auto load_w = [&](int mo, u32x4 (&wf)[WF]) __attribute__((always_inline)) {
+        const int f = qs * HQ + (F32 ? 4 : 8) * g, o = 16 * mo + q;
+        constexpr int step = F32 ? 16 : 32;
 #pragma unroll
-        for (int m = 0; m < MQ; ++m) {
-          if (REV) {
-            wf[m] = *reinterpret_cast<const f32x4*>(W + ((size_t)e * H + o) * H + f + 16 * m);
-          } else if (Wt != nullptr) {
-            wf[m] = *reinterpret_cast<const f32x4*>(Wt + ((size_t)e * H + o) * H + f + 16 * m);
-          } else {
+        for (int m = 0; m < WF; ++m) {
+          if (REV || Wt != nullptr) {
+            wf[m] = *reinterpret_cast<const u32x4*>((REV ? W : Wt) + ((size_t)e * H + o) * H + f + step * m);
+          } else {   // a column of W_e
+            const S* p = W + ((size_t)e * H + f + step * m) * H + o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) wf[m][i] = W[((size_t)e * H + f + 16 * m + i) * H + o];
+            for (int i = 0; i < 4; ++i) {
+              if constexpr (F32)
+                wf[m][i] = __float_as_uint(p[(size_t)i * H]);
+              else
+                wf[m][i] = static_cast<uint32_t>(p[(size_t)(2 * i) * H]) |
+                           (static_cast<uint32_t>(p[(size_t)(2 * i + 1) * H]) << 16);
+            }
           }
         }
       };
-      f32x4 wf[2][GM < MT ? GM : MT][MQ];
-      constexpr int GMT = GM < MT ? GM : MT;
+      u32x4 wf[2][GMT][WF];
 #pragma unroll
       for (int i = 0; i < GMT; ++i) load_w(i, wf[0][i]);   // in flight during the aggregation
 
@@ -247,7 +305,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
         uint32_t any = 0u;
 #pragma unroll
         for (int n = 0; n < NTW; ++n) any |= cur[s][n].any();
-        if (!split_any(any)) continue;   // no edge of this type from the block into the wave's rows
+        if (!direct_any(any)) continue;   // no edge of this type from the block into the wave's rows
         if constexpr (RB == 4 || RB == 8) {
 #pragma unroll
           for (int n = 0; n < NTW; ++n) bytes_to_contiguous<RB>(cur[s][n].w, godd);
@@ -259,13 +317,13 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
             uint32_t step = 0u;
 #pragma unroll
             for (int n = 0; n < NTW; ++n) step |= cur[s][n].byte(kk);
-            if (!split_any(step)) continue;
+            if (!direct_any(step)) continue;
           }
           bf16x8 bf[NTW];
 #pragma unroll
-          for (int n = 0; n < NTW; ++n) bf[n] = split_bits_frag(cur[s][n].byte(kk));
+          for (int n = 0; n < NTW; ++n) bf[n] = direct_bits_frag(cur[s][n].byte(kk));
 #pragma unroll
-          for (int p = 2; p >= 0; --p)   // the small parts first
+          for (int p = C::PARTS - 1; p >= 0; --p)   // the small parts first
 #pragma unroll
             for (int m = 0; m < MQ; ++m) {
               const bf16x8 af = load_fragi<bf16s>(xb + p * C::PLANE, kk * MQ + m, lane);
@@ -274,15 +332,42 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
             }
         }
       }
-      if constexpr (REV) {
+      // The aggregate as operand: fp32 the accumulators themselves; bf16
+      // fragments of eight features, forward as hi + lo, reverse rounded (the
+      // stored dM).
+      constexpr int NP = REV ? 1 : 2;
+      bf16x8 pf[F32 ? 1 : NP][NTW][F32 ? 1 : WF];
+      if constexpr (!F32) {
 #pragma unroll
         for (int n = 0; n < NTW; ++n)
 #pragma unroll
-          for (int m = 0; m < MQ; ++m)
-            *reinterpret_cast<f32x4*>(dM + ((size_t)e * ldm + (size_t)k * B + rw + 16 * n + q) * H + qs * HQ +
-                                      16 * m + 4 * g) = P[n][m];
+          for (int kk = 0; kk < WF; ++kk) {
+            float v8[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              v8[j] = P[n][2 * kk][j];
+              v8[4 + j] = P[n][2 * kk + 1][j];
+            }
+            if constexpr (REV)
+              pf[0][n][kk] = pack8<bf16s>(v8);
+            else
+              split8(v8, pf[0][n][kk], pf[NP - 1][n][kk]);
+          }
       }
-      // acc[n][mo] += W rows x aggregate (accumulators straight as operands)
+      if constexpr (REV) {
+#pragma unroll
+        for (int n = 0; n < NTW; ++n) {
+          S* row = dM + ((size_t)e * ldm + (size_t)k * B + rw + 16 * n + q) * H + qs * HQ + (F32 ? 4 : 8) * g;
+#pragma unroll
+          for (int m = 0; m < WF; ++m) {
+            if constexpr (F32)
+              *reinterpret_cast<f32x4*>(row + 16 * m) = P[n][m];
+            else
+              *reinterpret_cast<bf16x8*>(row + 32 * m) = pf[0][n][m];
+          }
+        }
+      }
+      // acc[n][mo] += W rows x aggregate
 #pragma unroll
       for (int mo = 0; mo < MT; mo += GMT) {
         const int b = (mo / GMT) & 1;
@@ -291,14 +376,26 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
           for (int i = 0; i < GMT; ++i) load_w(mo + GMT + i, wf[1 - b][i]);
         }
 #pragma unroll
-        for (int m = 0; m < MQ; ++m)
+        for (int m = 0; m < WF; ++m) {
+          if constexpr (F32) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int i = 0; i < GMT; ++i)
+              for (int i = 0; i < GMT; ++i)
 #pragma unroll
-              for (int n = 0; n < NTW; ++n)
-                acc[n][mo + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[b][i][m][j], P[n][m][j], acc[n][mo + i], 0, 0, 0);
+                for (int n = 0; n < NTW; ++n)
+                  acc[n][mo + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wf[b][i][m][j]), P[n][m][j],
+                                                                        acc[n][mo + i], 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int part = 0; part < NP; ++part)
+#pragma unroll
+              for (int i = 0; i < GMT; ++i)
+#pragma unroll
+                for (int n = 0; n < NTW; ++n)
+                  mma(acc[n][mo + i], __builtin_bit_cast(bf16x8, wf[b][i][m]), pf[part][n][m]);
+          }
+        }
       }
       if (!REV && bias != nullptr && qs == 0) {
 #pragma unroll
@@ -358,11 +455,9 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_split_kernel(
 
 }  // namespace dev
 
-#ifndef GGNN_SPLIT_SMALL_TILES
-#define GGNN_SPLIT_SMALL_TILES 512
-#endif
 namespace {
-struct SplitArgs {
+using S = dev::dt_t;
+struct DirectArgs {
   bool rev;
   const void *bits, *V, *W, *Wt;
   const float* bias;
@@ -374,22 +469,36 @@ struct SplitArgs {
 };
 
 template <int H, int B, int WAVES, int TG>
-hipError_t split_launch(const SplitArgs& A, hipStream_t st) {
-  using C = dev::SplitCfg<H, B, WAVES, TG>;
+hipError_t direct_launch(const DirectArgs& A, hipStream_t st) {
+  using C = dev::DirectCfg<S, H, B, WAVES, TG>;
   const dim3 grid((unsigned)(A.n_pad / C::R)), block(C::NT);
   if (A.rev)
-    hipLaunchKernelGGL((dev::step_split_kernel<H, B, WAVES, TG, true>), grid, block, 0, st,
-                       static_cast<const uint8_t*>(A.bits), static_cast<const float*>(A.V),
-                       static_cast<const float*>(A.W), nullptr, nullptr, A.out, A.n_pad, A.E, A.dX_in,
-                       static_cast<float*>(A.dM), A.ldm);
+    hipLaunchKernelGGL((dev::step_direct_kernel<S, H, B, WAVES, TG, true>), grid, block, 0, st,
+                       static_cast<const uint8_t*>(A.bits), static_cast<const S*>(A.V), static_cast<const S*>(A.W),
+                       nullptr, nullptr, A.out, A.n_pad, A.E, A.dX_in, static_cast<S*>(A.dM), A.ldm);
   else
-    hipLaunchKernelGGL((dev::step_split_kernel<H, B, WAVES, TG, false>), grid, block, 0, st,
-                       static_cast<const uint8_t*>(A.bits), static_cast<const float*>(A.V),
-                       static_cast<const float*>(A.W), static_cast<const float*>(A.Wt), A.bias, A.out, A.n_pad, A.E,
-                       nullptr, nullptr, 0L);
+    hipLaunchKernelGGL((dev::step_direct_kernel<S, H, B, WAVES, TG, false>), grid, block, 0, st,
+                       static_cast<const uint8_t*>(A.bits), static_cast<const S*>(A.V), static_cast<const S*>(A.W),
+                       static_cast<const S*>(A.Wt), A.bias, A.out, A.n_pad, A.E, nullptr, nullptr, 0L);
   return hipGetLastError();
 }
 
+#if GGNN_DT_BF16
+// As below; T = 2 passes of 8 types with one, two and four row tiles per workgroup: H = 128, B = 128: 145 / 181 / 251
+// us at 63 tiles, 257 / 235 / 308 at 375, 452 / 413 / 395 at 938 (H = 64, B = 256: 93 / 104 / 126, 151 / 129 / 152,
+// 259 / 214 / 193).
+template <int H, int B>
+hipError_t direct_pick(const DirectArgs& A, hipStream_t st) {
+  const int tiles = A.n_pad / 32;
+  if constexpr (B >= 128) {
+    if (tiles > 512) return direct_launch<H, B, 4, 2>(A, st);
+  }
+  if constexpr (B >= 64) {
+    if (tiles > 128) return direct_launch<H, B, 2, 4>(A, st);
+  }
+  return direct_launch<H, B, 1, 8>(A, st);
+}
+#else
 // Rows and type groups of a workgroup, by the number of 32-row tiles.  Few
 // tiles: one per workgroup and eight type groups, so that the compute units
 // fill up and a wave walks few types; many: more rows share a staged window.
@@ -397,40 +506,41 @@ hipError_t split_launch(const SplitArgs& A, hipStream_t st) {
 // form: 112 / 145 us at 250 tiles, 154 / 161 us at 500, 246 / 205 us at 1000
 // (H = 32: 55 / 67, 65 / 72, 97 / 87; H = 128: 303 / 400, 405 / 437, 698 / 603).
 template <int H, int B>
-hipError_t split_pick(const SplitArgs& A, hipStream_t st) {
+hipError_t direct_pick(const DirectArgs& A, hipStream_t st) {
   const int tiles = A.n_pad / 32;
-  if (tiles <= GGNN_SPLIT_SMALL_TILES) return split_launch<H, B, 1, 8>(A, st);
-  if constexpr (B == 32) return split_launch<H, B, 1, 2>(A, st);
-  if constexpr (B == 64) return split_launch<H, B, 2, 2>(A, st);
-  if constexpr (B >= 128) return split_launch<H, B, 4, 2>(A, st);
+  if (tiles <= 512) return direct_launch<H, B, 1, 8>(A, st);
+  if constexpr (B == 32) return direct_launch<H, B, 1, 2>(A, st);
+  if constexpr (B == 64) return direct_launch<H, B, 2, 2>(A, st);
+  if constexpr (B >= 128) return direct_launch<H, B, 4, 2>(A, st);
 }
+#endif
 
 template <int H>
-hipError_t split_h(int B, const SplitArgs& A, hipStream_t st) {
+hipError_t direct_h(int B, const DirectArgs& A, hipStream_t st) {
   switch (B) {
-    case 32: return split_pick<H, 32>(A, st);
-    case 64: return split_pick<H, 64>(A, st);
-    case 128: return split_pick<H, 128>(A, st);
-    case 256: return split_pick<H, 256>(A, st);
-    case 512: return split_pick<H, 512>(A, st);
+    case 32: return direct_pick<H, 32>(A, st);
+    case 64: return direct_pick<H, 64>(A, st);
+    case 128: return direct_pick<H, 128>(A, st);
+    case 256: return direct_pick<H, 256>(A, st);
+    case 512: return direct_pick<H, 512>(A, st);
   }
   return hipErrorInvalidValue;
 }
 }  // namespace
 
-namespace impl_f32 {
-hipError_t launch_step_split(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V, const void* W,
-                             const void* Wt, const float* bias, float* out, const float* dX_in, void* dM, long ldm,
-                             hipStream_t st) {
-  const SplitArgs A{rev, bits, V, W, Wt, bias, out, dX_in, dM, ldm, n_pad, E};
+namespace GGNN_IMPL_NS {
+hipError_t launch_step_direct(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V,
+                              const void* W, const void* Wt, const float* bias, float* out, const float* dX_in,
+                              void* dM, long ldm, hipStream_t st) {
+  const DirectArgs A{rev, bits, V, W, Wt, bias, out, dX_in, dM, ldm, n_pad, E};
   switch (H) {
-    case 32: return split_h<32>(B, A, st);
-    case 64: return split_h<64>(B, A, st);
-    case 128: return split_h<128>(B, A, st);
-    case 256: return split_h<256>(B, A, st);
+    case 32: return direct_h<32>(B, A, st);
+    case 64: return direct_h<64>(B, A, st);
+    case 128: return direct_h<128>(B, A, st);
+    case 256: return direct_h<256>(B, A, st);
   }
   return hipErrorInvalidValue;
 }
-}  // namespace impl_f32
+}  // namespace GGNN_IMPL_NS
 
 }  // namespace ggnn

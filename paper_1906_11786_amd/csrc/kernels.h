@@ -111,7 +111,10 @@ struct SnStep {
   bool step_wide_applies(int B, int H);                                                                           \
   hipError_t launch_step_wide(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V,          \
                               const void* Wsrc, const float* bias, float* out, const float* dX_in, void* dM,      \
-                              long ldm, hipStream_t st);
+                              long ldm, hipStream_t st);                                                          \
+  hipError_t launch_step_direct(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V,        \
+                                const void* W, const void* Wt, const float* bias, float* out, const float* dX_in, \
+                                void* dM, long ldm, hipStream_t st);
 
 namespace impl_bf16 {
 GGNN_DT_LAUNCHERS
@@ -141,10 +144,6 @@ hipError_t launch_step_bwd_bits_sn(int n_pad, int B, int H, int E, const void* b
 }
 namespace impl_f32 {
 GGNN_DT_LAUNCHERS
-// The fused bit-band step in fp32, forward (Wt = W_e^T or NULL) or reverse.
-hipError_t launch_step_split(bool rev, int n_pad, int B, int H, int E, const void* bits, const void* V, const void* W,
-                             const void* Wt, const float* bias, float* out, const float* dX_in, void* dM, long ldm,
-                             hipStream_t st);
 }
 #undef GGNN_DT_LAUNCHERS
 
@@ -167,11 +166,31 @@ hipError_t launch_reduce_partials(const float* part, float* out, int nsplit, int
                                   hipStream_t st);
 hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 
+// Whether a bit-band step runs as the direct-weight kernel (csrc/banded_direct.hip): always in fp32; in bf16
+//   where the fused narrow kernel would stream its blocks once per edge type (H = 64 at B >= 256, H = 32 at
+//     B = 512): 657 -> 300 us for a pass at H = 64, B = 256 and 100,000 nodes, 515 -> 93 us (T = 2) at 2,000;
+//   the reverse up to 128 row tiles of 32 nodes at H = 64, B = 64 or 128 and H = 32, B = 256, where it and the GRU's
+//     own launch beat the fused step with its few waves (both directions at T = 4, H = 64, B = 128: 182 -> 163 us at
+//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000); at smaller B (H = 64, B = 32, 2,000 nodes: 74
+//     against 77 us) and in the forward (2,000 nodes, 8 steps: 139 against 146) the fused step stays ahead;
+//   at H = 128 up to 1,024 tiles (T = 2, B = 128: 383 -> 145 us at 2,000 nodes, 431 -> 235 at 12,000, 500 -> 395 at
+//     30,000; 407 -> 418 at 65,000 with T = 1), at H = 256 up to 512 (B = 128, T = 1: 483 -> 400 us at 16,000 nodes,
+//     495 -> 588 at 20,000), 1,024 at B = 512 (1,090 -> 709 at 20,000; 1,367 -> 1,470 at 60,000): with more
+//     rows the wide kernel's sharing of every weight between the rows of a block pays.
+inline bool step_direct(int dt, int n_pad, int B, int H, bool rev) {
+  const int tiles = n_pad / 32;
+  if (dt == GGNN_F32) return true;
+  if (H == 32) return B == 512 || (rev && B == 256 && tiles <= 128);
+  if (H == 64) return B >= 256 || (rev && B >= 64 && tiles <= 128);
+  return tiles <= (H == 128 || B == 512 ? 1024 : 512);
+}
+
 // 1-bit band: fused aggregate-first forward and transposed-band reverse.
 inline hipError_t launch_step_fwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits, const void* X,
                                        const void* W, const float* bias, float* a, hipStream_t st) {
-  if (dt == GGNN_F32)
-    return impl_f32::launch_step_split(false, n_pad, B, H, E, bits, X, W, nullptr, bias, a, nullptr, nullptr, 0, st);
+  if (step_direct(dt, n_pad, B, H, false))
+    return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, nullptr, bias, a, nullptr, nullptr, 0,
+                        st);
   return impl_bf16::launch_step_fwd_bits(n_pad, B, H, E, bits, X, W, bias, a, st);
 }
 inline hipError_t launch_banded_bwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits_t, const void* da,
@@ -191,13 +210,13 @@ inline hipError_t launch_step_fwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* W, const void* Wt, const float* bias, float* a,
                                            const void* Wi, const void* U, const float* bg, void* h_out, void* saved,
                                            bool* fused, hipStream_t st) {
+  if (step_direct(dt, n_pad, B, H, false)) {
+    if (fused) *fused = false;
+    return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
+  }
   if (Wt != nullptr && step_wide(dt, B, H)) {
     if (fused) *fused = false;
     return impl_bf16::launch_step_wide(false, n_pad, B, H, E, bits, X, Wt, bias, a, nullptr, nullptr, 0, st);
-  }
-  if (dt == GGNN_F32) {
-    if (fused) *fused = false;
-    return impl_f32::launch_step_split(false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
   }
   return impl_bf16::launch_step_fwd_bits_gru(n_pad, B, H, E, bits, X, W, Wt, bias, a, Wi, U, bg, h_out, saved, fused,
                                              st);
@@ -215,14 +234,14 @@ inline hipError_t launch_step_bwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* Wi, const void* U, const void* h_prev, const void* saved_prev,
                                            void* da_prev, float* dh_prev, void* ghat_prev, bool* fused,
                                            hipStream_t st) {
+  if (dX_out != nullptr && step_direct(dt, n_pad, B, H, true)) {
+    if (fused) *fused = false;
+    return GGNN_DT_PICK(launch_step_direct, true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM,
+                        ldm, st);
+  }
   if (dX_out != nullptr && step_wide(dt, B, H)) {
     if (fused) *fused = false;
     return impl_bf16::launch_step_wide(true, n_pad, B, H, E, bits_t, da, W, nullptr, dX_out, dX_in, dM, ldm, st);
-  }
-  if (dt == GGNN_F32) {
-    if (fused) *fused = false;
-    return impl_f32::launch_step_split(true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM, ldm,
-                                       st);
   }
   return impl_bf16::launch_step_bwd_bits_gru(n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, Wi, U, h_prev,
                                              saved_prev, da_prev, dh_prev, ghat_prev, fused, st);
@@ -232,11 +251,11 @@ inline hipError_t launch_step_bwd_bits_gru(int dt, int n_pad, int B, int H, int 
 inline hipError_t launch_step_bwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits_t, const void* da,
                                        const void* W, const float* dX_in, float* dX_out, void* dM, long ldm,
                                        hipStream_t st) {
+  if (step_direct(dt, n_pad, B, H, true))
+    return GGNN_DT_PICK(launch_step_direct, true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM,
+                        ldm, st);
   if (step_wide(dt, B, H))
     return impl_bf16::launch_step_wide(true, n_pad, B, H, E, bits_t, da, W, nullptr, dX_out, dX_in, dM, ldm, st);
-  if (dt == GGNN_F32)
-    return impl_f32::launch_step_split(true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM, ldm,
-                                       st);
   return impl_bf16::launch_step_bwd_bits(n_pad, B, H, E, bits_t, da, W, dX_in, dX_out, dM, ldm, st);
 }
 

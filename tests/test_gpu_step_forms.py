@@ -72,6 +72,20 @@ def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
     _step_case("f32", B, H, E, nb, B + H + E, bias)
 
 
+# bf16: the direct-weight kernel's three workgroup forms (up to 128 row tiles of 32 nodes, up to 512, more), both
+# sides of the sizes where another kernel takes over (H = 64: 128 tiles at B <= 128).
+@pytest.mark.parametrize("B,H,E,nb,bias", [
+    (64, 64, 9, 64, True), (64, 64, 3, 65, True), (128, 64, 10, 32, False), (128, 64, 3, 33, False),
+    (256, 64, 5, 3, True), (256, 64, 2, 20, False), (256, 64, 2, 65, True), (512, 32, 3, 2, True), (512, 32, 1, 33, False),
+    (256, 32, 2, 16, True), (32, 128, 3, 4, True), (32, 128, 2, 520, False), (64, 128, 1, 260, True),
+    (128, 128, 9, 2, False), (128, 128, 2, 40, True), (128, 128, 2, 130, True), (256, 128, 2, 17, False),
+    (512, 128, 1, 33, True), (32, 256, 3, 5, True), (64, 256, 2, 70, False), (128, 256, 1, 40, True),
+    (256, 256, 2, 1, True), (512, 256, 1, 2, True)])
+def test_bf16_step_forms_integer_exact(B, H, E, nb, bias):
+    say(f"bf16 step form B={B} H={H} E={E} nb={nb} bias={bias}")
+    _step_case("bf16", B, H, E, nb, B + H + E, bias)
+
+
 @pytest.mark.parametrize("B", [32, 128, 512])
 def test_f32_step_keeps_every_bit(B):
     """One message per node through W = I: the aggregate is the sender's state, bit for bit, over the whole
