@@ -153,9 +153,10 @@ hipError_t readout_bwd_h(int n_pad, int n_cand, const void* X, const float* w_ou
                      cand_node, dlogit, n_cand, part);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  err = launch_reduce_partials(part, dw_out, ns, H, H + 1, st);
-  if (err != hipSuccess) return err;
-  return launch_reduce_partials(part + H, db_out, ns, 1, H + 1, st);
+  ReduceList red;   // dw_out and db_out in one launch
+  red.seg[red.n++] = ReduceSeg{part, dw_out, ns, H, H + 1};
+  red.seg[red.n++] = ReduceSeg{part + H, db_out, ns, 1, H + 1};
+  return launch_reduce_multi(red, st);
 }
 }  // namespace
 

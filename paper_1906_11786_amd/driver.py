@@ -150,14 +150,34 @@ class BandedGGNN:
             t0 = time.perf_counter()
             self.band = band_to_device(band, dt, device)
             del band
-        self.W = to_device(params.W, dt, device)
+        # All parameters, gradients and optimizer state lie in flat buffers of
+        # one layout (each view starts on a 64-float boundary, the gaps hold
+        # zeros), so that one fill clears the gradients and one Momentum launch
+        # updates every parameter: `master` float32, `compute_copy` in bf16 (the
+        # propagation reads W, Wi, U there and the rest in `master`; in fp32
+        # everything is read in `master`).
+        sizes = [E * H * H, E * H, H * 3 * H, H * 3 * H, 3 * H, H, 1]   # W, bias, Wi, U, b, w_out, b_out
+        offs = [0]
+        for s_ in sizes:
+            offs.append(offs[-1] + -(-s_ // 64) * 64)
+        self._layout = list(zip(offs, sizes))
+        self.master = torch.zeros((offs[-1],), dtype=torch.float32, device=device)
+        self.compute_copy = torch.zeros((offs[-1],), dtype=td, device=device) if dt == "bf16" else None
+        states = self.master if self.compute_copy is None else self.compute_copy
+        self.W = self._views(states)[0].view(E, H, H)
+        self.W.copy_(to_device(params.W, dt, device))
         # W_e^T, an optional operand of the bit-band forward (row reads of its
         # weight fragments); refreshed from W by refresh_weights().
         self.Wt = torch.empty_like(self.W)
-        self.bias = None if params.bias is None else torch.from_numpy(params.bias.astype(np.float32)).to(device)
-        self.Wi = to_device(params.Wi, dt, device)
-        self.U = to_device(params.U, dt, device)
-        self.b = torch.from_numpy(params.b.astype(np.float32)).to(device)
+        self.bias = None
+        if params.bias is not None:
+            self.bias = self._views(self.master)[1].view(E, H)
+            self.bias.copy_(torch.from_numpy(params.bias.astype(np.float32)))
+        self.Wi, self.U = (self._views(states)[i].view(H, 3 * H) for i in (2, 3))
+        self.Wi.copy_(to_device(params.Wi, dt, device))
+        self.U.copy_(to_device(params.U, dt, device))
+        self.b = self._views(self.master)[4]
+        self.b.copy_(torch.from_numpy(params.b.astype(np.float32)))
         # Wi, U in the staging order of the large-width GRU kernels, refreshed
         # with Wt; absent where no kernel reads it.
         pk = capi.ggnn_gru_pack_bytes(dt, H) if gru_pack else 0
@@ -170,15 +190,10 @@ class BandedGGNN:
                   else None)
         self.G = torch.from_numpy(params.G.astype(np.float32)).to(device)
         self.dX = torch.empty((n_pad, H), dtype=torch.float32, device=device)
-        # All weight gradients in one buffer (one fill clears them), each
-        # view starting on a 64-float boundary; the last two are the readout's
-        # (w_out, b_out), used by train_step().
-        sizes = [E * H * H, E * H, H * 3 * H, H * 3 * H, 3 * H, H, 1]
-        offs = [0]
-        for s_ in sizes:
-            offs.append(offs[-1] + -(-s_ // 64) * 64)
-        self.grad_buf = torch.zeros((offs[-1],), dtype=torch.float32, device=device)
-        views = [self.grad_buf[o:o + s_] for o, s_ in zip(offs, sizes)]
+        # The weight gradients; the last two are the readout's (w_out, b_out),
+        # used by train_step().
+        self.grad_buf = torch.zeros_like(self.master)
+        views = self._views(self.grad_buf)
         self.dW = views[0].view(E, H, H)
         self.dbias = views[1].view(E, H)
         self.dWi = views[2].view(H, 3 * H)
@@ -213,6 +228,10 @@ class BandedGGNN:
             dU=self.dU.data_ptr(), db=self.db.data_ptr(), da=self.da.data_ptr(), dM=self.dM.data_ptr(),
             dh=self.dh.data_ptr(), workspace=self.workspace.data_ptr(), workspace_bytes=self.workspace.numel())
         comp.stats["upload_seconds"] = time.perf_counter() - t0
+
+    def _views(self, flat):
+        """Flat views of W, bias, Wi, U, b, w_out and b_out in a buffer of the parameter layout."""
+        return [flat[o:o + n] for o, n in self._layout]
 
     def refresh_weights(self, stream=None):
         """Recompute W_e^T and the packed GRU weights after W, Wi or U change."""
@@ -276,8 +295,10 @@ class BandedGGNN:
         self.target = torch.from_numpy(np.ascontiguousarray(cands.target, np.int32)).to(dev)
         self.n_graphs = len(cands.ptr) - 1
         self.n_cand = int(cands.ptr[-1])
-        self.w_out = torch.from_numpy(np.asarray(w_out, np.float32)).to(dev)
-        self.b_out = torch.tensor([b_out], dtype=torch.float32, device=dev)
+        masters = self._views(self.master)
+        self.w_out, self.b_out = masters[5], masters[6]
+        self.w_out.copy_(torch.from_numpy(np.asarray(w_out, np.float32)))
+        self.b_out.fill_(float(b_out))
         self.logits = torch.empty((max(self.n_cand, 1),), dtype=torch.float32, device=dev)
         self.dlogit = torch.empty_like(self.logits)
         self.loss = torch.empty((self.n_graphs,), dtype=torch.float32, device=dev)
@@ -285,16 +306,18 @@ class BandedGGNN:
         self.readout_ws = torch.empty((max(ws, 16),), dtype=torch.uint8, device=dev)
         self.opt = dict(lr=lr, momentum=momentum, weight_decay=weight_decay, nesterov=nesterov)
         # (master float32, velocity, gradient, compute copy or None)
-        bf = self.dt == "bf16"
-        entries = [(self.W, self.dW), (self.Wi, self.dWi), (self.U, self.dU), (self.b, self.db),
-                   (self.w_out, self.dw_out), (self.b_out, self.db_out)]
+        self.velocity = torch.zeros_like(self.master)
+        vels = self._views(self.velocity)
+        entries = [(0, self.W, self.dW), (2, self.Wi, self.dWi), (3, self.U, self.dU), (4, self.b, self.db),
+                   (5, self.w_out, self.dw_out), (6, self.b_out, self.db_out)]
         if self.bias is not None:
-            entries.append((self.bias, self.dbias))
+            entries.append((1, self.bias, self.dbias))
         self.param_state = []
-        for t, g in entries:
-            copy = t if (bf and t.dtype != torch.float32) else None
-            master = t.float().clone() if copy is not None else t
-            self.param_state.append((master, torch.zeros_like(master), g, copy))
+        for i, t, g in entries:
+            copy = t if t.dtype != torch.float32 else None
+            if copy is not None:
+                masters[i].copy_(t.reshape(-1))
+            self.param_state.append((masters[i].view(t.shape), vels[i].view(t.shape), g, copy))
 
     def readout(self, stream=None):
         """Logits, per-graph losses and d(mean loss)/d(logits) of X_T."""
@@ -314,9 +337,8 @@ class BandedGGNN:
                                    self.readout_ws.numel(), stream)
         capi.ggnn_backward(self.model, self.act, self.grads, stream)
         o = self.opt
-        for master, vel, g, copy in self.param_state:
-            capi.ggnn_sgd_momentum(master.numel(), master, vel, g, o["lr"], o["momentum"], o["weight_decay"],
-                                   o["nesterov"], self.dt, copy, stream)
+        capi.ggnn_sgd_momentum(self.master.numel(), self.master, self.velocity, self.grad_buf, o["lr"],
+                               o["momentum"], o["weight_decay"], o["nesterov"], self.dt, self.compute_copy, stream)
         self.refresh_weights(stream)
 
     # --------------------------------------------- evaluation on every edge

@@ -162,3 +162,32 @@ def test_sparse_step_forms_integer_exact(dt, H, E, n):
                           dev(X, dt), dev(W.transpose(0, 2, 1), dt), None if bias is None else dev(bias), a)
     s, d, e, _ = O.dedupe_edges(src, dst, et)
     np.testing.assert_array_equal(host(a), O.aggregate(n, s, d, e, O.msg_transform(X, W, bias)))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_parameters_keep_their_addresses(dt):
+    """The parameters a captured pass reads are the ones a training step updates, also when training is set up
+    after the capture; the flat buffers' gaps stay zero."""
+    from ggnn_synth import backbone_graph, draw_candidates, draw_params, draw_readout
+    from paper_1906_11786_amd.driver import BandedGGNN, compile_graphs
+    E, H, n = 3, 32, 200
+    comp = compile_graphs([backbone_graph(5, 0, n, E, span_mean=4.0, max_span=30)], 32, E, reorder=False)
+    m = BandedGGNN(comp, H, 2, dt, draw_params(5, n, comp.n_pad, H, E, dt, with_bias=True))
+    m.capture()
+    before = [t.data_ptr() for t in (m.W, m.bias, m.Wi, m.U, m.b)]
+    cands = draw_candidates(5, comp.offsets)
+    m.setup_training(cands, *draw_readout(5, H), lr=0.1, momentum=0.9, weight_decay=0.01)
+    m.train_step()
+    assert before == [t.data_ptr() for t in (m.W, m.bias, m.Wi, m.U, m.b)]
+    m.step()
+    eager = {k: v.copy() for k, v in m.results().items()}
+    for _ in range(3):
+        m.X[1:].zero_()
+        m.replay()
+        torch.cuda.synchronize()
+        for k, v in m.results().items():
+            np.testing.assert_array_equal(v, eager[k])
+    used = torch.zeros_like(m.master, dtype=torch.bool)
+    for v in m._views(used):
+        v.fill_(True)
+    assert not m.master[~used].any() and not m.velocity[~used].any()
