@@ -76,7 +76,7 @@ KERNELS = {
     "banded_propagate_bwd": (("banded_bwd_kernel",), ["banded.hip", "device_common.h"]),
 }
 # Other kernels of the step, listed in the traffic summary.
-OTHER_KERNELS = [("step_direct_kernel",), ("gru_fwd_kernel",), ("gru_bwd_kernel",), ("gru_fwd_cols_kernel",), ("gru_bwd_big_kernel",),
+OTHER_KERNELS = [("step_direct_kernel",), ("gru_fwd_kernel",), ("gru_bwd_kernel",), ("gru_fwd_cols_kernel",), ("gru_bwd_cols_kernel",),
                  ("gru_wgrad_kernel",), ("gru_wgrad256_kernel",), ("transform_bwd_dx_kernel",),
                  ("transform_wgrad_kernel",), ("transform_wgrad_nm_kernel",), ("transform_fwd_kernel",),
                  ("transform_wgrad_nm256_kernel",), ("reduce_partials_kernel",), ("reduce_multi_kernel",)]

@@ -221,26 +221,15 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_bwd_kernel(const float* __r
 
 // ---------------------------------------------------------------------------
 // Packed weights of the large-H kernels (H >= 128): lane vectors of eight
-// elements (16 bytes) back to back in the order the kernels read them.
+// elements (16 bytes) back to back in the order the kernels read them,
 //   forward: fragment (feature group fw, matrix c of Wi_r, U_r, Wi_z, U_z,
 //     Wi_n, U_n, k step kk, tile i), lane (qq, gg): gate column
 //     32 fw + 2 qq + i at input rows 32 kk + 8 gg + {0..7};
-//   the reverse streams Wi and U through LDS in stages, unit `lin` of a stage
-//   landing at element 8 lin of the stage buffer:
-//   reverse pass 1, block m: U rows 16m.., gate n, fragments kk;
-//   reverse pass 2, block m: Wi rows 16m.., gates r, z, n, then U gates r, z;
-//     unit (gate, kk, lane (qq, gg)): row 16m + qq at gate columns
-//     32kk + 4gg + {0..3}, 32kk + 16 + 4gg + {0..3}.
+//   reverse, after it: fragment (feature group fw, matrix c of U_n, Wi_r,
+//     Wi_z, Wi_n, U_r, U_z, k step kk, tile i), lane (qq, gg): input row
+//     32 fw + 2 qq + i at gate columns 32 kk + 8 gg + {0..7}.
 // ---------------------------------------------------------------------------
-template <int H>
-struct GruPack {
-  static constexpr int KS = H / 32, NC = H / 16, FRU = KS * 64;   // units per 16-wide block
-  static constexpr int UNITS = 6 * NC * FRU;                      // units per region (6 H^2 / 8)
-  // first unit of reverse block m of pass p
-  __host__ __device__ static constexpr int rev_stage(int p, int m) {
-    return p == 1 ? m * FRU : NC * FRU + 5 * m * FRU;
-  }
-};
+__host__ __device__ constexpr int gru_pack_units(int H) { return 6 * H * H / 8; }   // per direction
 
 template <typename S, int H>
 __device__ __forceinline__ u32x4 gru_fwd_unit(const S* __restrict__ Wi, const S* __restrict__ U, int u) {
@@ -256,56 +245,23 @@ __device__ __forceinline__ u32x4 gru_fwd_unit(const S* __restrict__ Wi, const S*
 }
 
 template <typename S, int H>
-__device__ __forceinline__ u32x4 gru_rev_unit(const S* __restrict__ Wi, const S* __restrict__ U, int pass, int m,
-                                              int lin) {
+__device__ __forceinline__ u32x4 gru_rev_unit(const S* __restrict__ Wi, const S* __restrict__ U, int u) {
   constexpr int KS = H / 32;
-  const int frag = lin / 64, l = lin % 64, qq = l % 16, gg = l / 16;
-  const S* mat;
-  int gate, kk;
-  if (pass == 1) {
-    mat = U;
-    gate = 2;
-    kk = frag;
-  } else if (frag < 3 * KS) {
-    mat = Wi;
-    gate = frag / KS;
-    kk = frag % KS;
-  } else {
-    mat = U;
-    gate = (frag - 3 * KS) / KS;
-    kk = (frag - 3 * KS) % KS;
-  }
-  const S* p = mat + (size_t)(16 * m + qq) * 3 * H + gate * H + 32 * kk + 4 * gg;
-  const u32x2 a = *reinterpret_cast<const u32x2*>(p);
-  const u32x2 b = *reinterpret_cast<const u32x2*>(p + 16);
-  return u32x4{a[0], a[1], b[0], b[1]};
+  const int l = u % 64, i = (u / 64) % 2, kk = (u / 128) % KS, c = (u / (128 * KS)) % 6, fw = u / (128 * KS * 6);
+  const int gate = c == 0 ? 2 : (c <= 3 ? c - 1 : c - 4);
+  const S* src = c >= 1 && c <= 3 ? Wi : U;
+  return *reinterpret_cast<const u32x4*>(src + (size_t)(32 * fw + 2 * (l % 16) + i) * 3 * H + gate * H + 32 * kk +
+                                         8 * (l / 16));
 }
 
 // One thread per unit: forward region, then reverse region.
 template <typename S, int H>
 __global__ __launch_bounds__(256) void gru_pack_kernel(const S* __restrict__ Wi, const S* __restrict__ U,
                                                        S* __restrict__ out) {
-  using P = GruPack<H>;
+  constexpr int UNITS = gru_pack_units(H);
   const int u = blockIdx.x * 256 + threadIdx.x;
-  if (u >= 2 * P::UNITS) return;
-  u32x4 v;
-  if (u < P::UNITS) {
-    v = gru_fwd_unit<S, H>(Wi, U, u);
-  } else {
-    const int x = u - P::UNITS;
-    int pass, m, lin;
-    if (x < P::NC * P::FRU) {
-      pass = 1;
-      m = x / P::FRU;
-      lin = x % P::FRU;
-    } else {
-      const int y = x - P::NC * P::FRU;
-      pass = 2;
-      m = y / (5 * P::FRU);
-      lin = y % (5 * P::FRU);
-    }
-    v = gru_rev_unit<S, H>(Wi, U, pass, m, lin);
-  }
+  if (u >= 2 * UNITS) return;
+  const u32x4 v = u < UNITS ? gru_fwd_unit<S, H>(Wi, U, u) : gru_rev_unit<S, H>(Wi, U, u - UNITS);
   *reinterpret_cast<u32x4*>(out + (size_t)u * 8) = v;
 }
 
@@ -355,8 +311,8 @@ __global__ __launch_bounds__(H / 32 * NW * kWave) void gru_fwd_cols_kernel(
 
   // Weights of k step kk, matrix c of (Wi_r, U_r, Wi_z, U_z, Wi_n, U_n): the two tiles' fragments from the packed
   // copy, or eight dwords of gate columns 32 fw + 2 q, + 1 at input features 32 kk + 8 g + {0..7}.
-  const auto rp = buffer_of(PK ? pk : Wi, PK ? 12 * H * H : 6 * H * H);
-  const auto ru = buffer_of(U, 6 * H * H);
+  const auto rp = buffer_of(PK ? pk : Wi, PK ? 6 * H * H : 3 * H * H);
+  const auto ru = buffer_of(U, 3 * H * H);
   const int woff = PK ? fw * 6 * KS * 2048 + lane * 16 : (8 * g * 3 * H + 32 * fw + 2 * q) * 2;
   auto load_w = [&](int c, int kk, uint32_t (&w)[8]) __attribute__((always_inline)) {
     if constexpr (PK) {
@@ -508,194 +464,176 @@ __global__ __launch_bounds__(H / 32 * NW * kWave) void gru_fwd_cols_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Backward for large H (bf16, H >= 128), the same arithmetic as
-// gru_bwd_wave, with the weights shared through LDS: a workgroup of 8 waves
-// (16 nodes each) streams the weights once per 128 nodes, in blocks of 16
-// input features (rows of Wi and U) kept in fragment order and double
-// buffered (the next block's loads are in flight during the current one).
-//   pass 1: q' = n^ U_n^T, block m gives q' for input features 16m..16m+15,
-//           hence r^ and the q' r term of dh for them;
-//   pass 2: block n gives da for input features 16n..16n+15 (G^ Wi^T, all
-//           three gates) and finishes dh for them (r^ U_r^T + z^ U_z^T).
+// Reverse in bf16 for H >= 128, the arithmetic of gru_bwd_wave in the form of
+// gru_fwd_cols_kernel: one wave per 32 input features for the workgroup's
+// 16 NTL nodes, G^ = [r^ z^ n^] of the nodes in LDS in fragment order, read by
+// the H / 32 feature waves, the weight rows straight from L2 (16-byte pieces
+// of 32 consecutive gate columns; or the packed fragments), each read once per
+// workgroup, one k step ahead of use.
+//   1: n^, z^ and g' z of the wave's features (the lane's eight);
+//   2: q' = n^ U_n^T, hence r^ and the q' r term of dh;
+//   3: da = G^ Wi^T as D[node][feature], dh += r^ U_r^T + z^ U_z^T.
+// Two consecutive node tiles interleave in fours (tile t, row m is node
+// 32 (t / 2) + 8 (m / 4) + 4 (t % 2) + m % 4), so that a lane holds eight
+// consecutive nodes of da's feature rows: 16-byte stores.  `dh` may be `gin`
+// (every element is read and written by the same lane).  Against one wave per
+// 16 nodes with the weights streamed through LDS, per launch: 12,352 nodes at
+// H = 128 20 -> 13 us, 65,536 at H = 128 57 -> 51 us, 262,144 at H = 256
+// 547 -> 523 us; 24 bytes per node and feature stream in about 320 us there.
 // ---------------------------------------------------------------------------
-template <typename S, int H, bool PK>
-__global__ __launch_bounds__(512) void gru_bwd_big_kernel(const float* __restrict__ gin, const S* __restrict__ h,
-                                                          const S* __restrict__ saved, const S* __restrict__ Wi,
-                                                          const S* __restrict__ U, const S* __restrict__ pk,
-                                                          S* __restrict__ daT,
-                                                          float* __restrict__ dh, S* __restrict__ ghat, int n_pad) {
-  static_assert(sizeof(S) == 2, "bf16 only");
-  constexpr int NT = 512, V = 8;
-  constexpr int KS = H / 32, MTL = H / 16;
-  // LDS per buffer: pass 1 the n-gate part of a U block; pass 2 a Wi block
-  // (three gates) and the r, z part of a U block, both in fragment order
-  // (index gate * KS + kk within the block).
-  constexpr int BLK_W = 3 * KS * 64 * 8, BLK_U = 2 * KS * 64 * 8;   // elements
-  // Pass 1 reads all of U_n (MTL blocks) from one staging, without barriers
-  // between blocks; pass 2's two block buffers then reuse the same LDS.
-  constexpr int P1E = MTL * KS * 64 * 8;                               // elements of U_n's blocks
-  constexpr int LDSE = P1E > 2 * (BLK_W + BLK_U) ? P1E : 2 * (BLK_W + BLK_U);
-  __shared__ __attribute__((aligned(16))) S lds_all[LDSE];
-  S (*lw)[BLK_W + BLK_U] = reinterpret_cast<S (*)[BLK_W + BLK_U]>(lds_all);
-
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+template <int H, int NTL, bool PK>
+__global__ __launch_bounds__(H / 32 * kWave) void gru_bwd_cols_kernel(
+    const float* gin, const bf16s* __restrict__ h, const bf16s* __restrict__ saved, const bf16s* __restrict__ Wi,
+    const bf16s* __restrict__ U, const bf16s* __restrict__ pk, bf16s* __restrict__ daT, float* dh,
+    bf16s* __restrict__ ghat, int n_pad) {
+  constexpr int KS = H / 32;
+  static_assert(NTL % 2 == 0, "node tiles come in pairs");
+  __shared__ __attribute__((aligned(16))) bf16s fr[3][NTL][KS][kWave * 8];   // r^, z^, n^
+  const int tid = threadIdx.x, fw = tid / kWave, lane = tid % kWave;
   const int q = lane % 16, g = lane / 16;
-  const int n0 = xcd_swizzle(blockIdx.x, gridDim.x) * 128 + 16 * wave;
-  const bool valid = n0 < n_pad;
-  const int node = n0 + q;
+  const int n0 = xcd_swizzle(blockIdx.x, gridDim.x) * 16 * NTL;
+  const int fe = 32 * fw + 8 * g;   // the lane's eight features: element e = 2 j + i (tile i, accumulator element j)
 
-  // Staging of weight block m (rows 16m .. 16m + 15) into buffer b:
-  // pass 1: U columns of gate n; pass 2: Wi all gates, U gates r, z; units as
-  // gru_rev_unit, from the packed reverse region when PK.
-  constexpr int U1 = KS * 64;                      // units, pass 1
-  constexpr int U2 = 5 * KS * 64;                  // pass 2: 3 KS fragments of Wi, 2 KS of U
-  constexpr int R2 = (U2 + NT - 1) / NT;
-  u32x4 rr[R2];
-  auto load_blk = [&](int pass, int m) __attribute__((always_inline)) {
+  // Weights of k step kk, matrix c of (U_n, Wi_r, Wi_z, Wi_n, U_r, U_z): rows 32 fw + 2 q + i, gate columns
+  // 32 kk + 8 g + {0..7}.
+  const auto rp = buffer_of(PK ? pk : Wi, 6 * H * H / (PK ? 1 : 2));
+  const auto ru = buffer_of(U, 3 * H * H);
+  const int woff = PK ? fw * 6 * KS * 2048 + lane * 16 : ((32 * fw + 2 * q) * 3 * H + 8 * g) * 2;
+  auto load_w = [&](int c, int kk, bf16x8 (&w)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < R2; ++u) {
-      const int lin = u * NT + tid;
-      if (lin < (pass == 1 ? U1 : U2)) {
-        if constexpr (PK)
-          rr[u] = *reinterpret_cast<const u32x4*>(pk + ((size_t)GruPack<H>::rev_stage(pass, m) + lin) * 8);
-        else
-          rr[u] = gru_rev_unit<S, H>(Wi, U, pass, m, lin);
+    for (int i = 0; i < 2; ++i) {
+      u32x4 v;
+      if constexpr (PK) {
+        v = __builtin_amdgcn_raw_buffer_load_b128(rp, woff, ((c * KS + kk) * 2 + i) * 1024, 0);
+      } else {
+        const int gate = c == 0 ? 2 : (c <= 3 ? c - 1 : c - 4);
+        v = __builtin_amdgcn_raw_buffer_load_b128(c >= 1 && c <= 3 ? rp : ru, woff,
+                                                  (i * 3 * H + gate * H + 32 * kk) * 2, 0);
       }
+      w[i] = __builtin_bit_cast(bf16x8, v);
     }
   };
-  auto store_blk = [&](int pass, int b) __attribute__((always_inline)) {
+  auto node_of = [&](int t) __attribute__((always_inline)) {
+    return n0 + 32 * (t / 2) + 8 * (q / 4) + 4 * (t % 2) + q % 4;
+  };
+  auto unpack8 = [&](const u32x4& v, float (&o)[8]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < R2; ++u) {
-      const int lin = u * NT + tid;
-      if (lin < (pass == 1 ? U1 : U2)) *reinterpret_cast<u32x4*>(&lw[b][lin * 8]) = rr[u];
-    }
+    for (int d = 0; d < 4; ++d) o[2 * d] = lo_f(v[d]), o[2 * d + 1] = hi_f(v[d]);
   };
 
-  // Pass 1's weights (all blocks of U_n, gate n), staged in rounds of R2
-  // units per thread; the first round's loads are in flight during phase 1.
-  constexpr int P1U = MTL * U1;
-  constexpr int P1R = (P1U + R2 * NT - 1) / (R2 * NT);
-  auto load_p1 = [&](int round) __attribute__((always_inline)) {
+  f32x4 acc[2][NTL];      // dh
+  u32x4 rraw[NTL], hraw[NTL];
+  bf16x8 w[2][2];
+  load_w(0, 0, w[0]);
 #pragma unroll
-    for (int u = 0; u < R2; ++u) {
-      const int lin = (round * R2 + u) * NT + tid;
-      if (lin < P1U) {
-        if constexpr (PK)
-          rr[u] = *reinterpret_cast<const u32x4*>(pk + ((size_t)GruPack<H>::rev_stage(1, 0) + lin) * 8);
-        else
-          rr[u] = gru_rev_unit<S, H>(Wi, U, 1, lin / U1, lin % U1);
-      }
+  for (int t = 0; t < NTL; ++t) {
+    const int node = min(node_of(t), n_pad - 1);   // past the end: a valid row whose results are not stored
+    const f32x4 g0 = *reinterpret_cast<const f32x4*>(gin + (size_t)node * H + fe),
+                g1 = *reinterpret_cast<const f32x4*>(gin + (size_t)node * H + fe + 4);
+    const bf16s* sv = saved + (size_t)node * 3 * H + fe;
+    rraw[t] = *reinterpret_cast<const u32x4*>(sv);
+    const u32x4 zr = *reinterpret_cast<const u32x4*>(sv + H), nr = *reinterpret_cast<const u32x4*>(sv + 2 * H);
+    hraw[t] = *reinterpret_cast<const u32x4*>(h + (size_t)node * H + fe);
+    float z[8], n[8], hv[8], zh[8], nh[8];
+    unpack8(zr, z);
+    unpack8(nr, n);
+    unpack8(hraw[t], hv);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float gg = e < 4 ? g0[e % 4] : g1[e % 4];
+      const float dn = gg * (1.f - z[e]), dz = gg * (hv[e] - n[e]);
+      acc[e & 1][t][e >> 1] = gg * z[e];
+      nh[e] = dn * (1.f - n[e] * n[e]);
+      zh[e] = dz * z[e] * (1.f - z[e]);
     }
-  };
-  auto store_p1 = [&](int round) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < R2; ++u) {
-      const int lin = (round * R2 + u) * NT + tid;
-      if (lin < P1U) *reinterpret_cast<u32x4*>(&lds_all[lin * 8]) = rr[u];
+    const bf16x8 pz = pack8<bf16s>(zh), pn = pack8<bf16s>(nh);
+    *reinterpret_cast<bf16x8*>(&fr[1][t][fw][lane * 8]) = pz;
+    *reinterpret_cast<bf16x8*>(&fr[2][t][fw][lane * 8]) = pn;
+    if (node_of(t) < n_pad) {
+      *reinterpret_cast<bf16x8*>(ghat + (size_t)node * 3 * H + H + fe) = pz;
+      *reinterpret_cast<bf16x8*>(ghat + (size_t)node * 3 * H + 2 * H + fe) = pn;
     }
-  };
-  load_p1(0);
-
-  // Phase 1 (elementwise, registers): n^, z^ as operand fragments, the
-  // g' z term of dh, and G^'s z, n columns.
-  frag_t<S> gf[3][KS];
-  f32x4 dacc[MTL];
-  const S* sv = saved + (size_t)node * 3 * H;
-  S* gh = ghat + (size_t)node * 3 * H;
-  if (valid) {
-    float zv[8], nv[8];
-    u32x2 zp[2], np[2], hp[2];   // tiles m, m + 1 of z, n, h (16-byte loads, load_tiles16)
-#pragma unroll
-    for (int m = 0; m < MTL; ++m) {
-      const int f = 16 * m + 4 * g;
-      const f32x4 gg = *reinterpret_cast<const f32x4*>(gin + (size_t)node * H + f);
-      if (m % 2 == 0) {
-        load_tiles16(sv + H + 16 * m, g, zp);
-        load_tiles16(sv + 2 * H + 16 * m, g, np);
-        load_tiles16(h + (size_t)node * H + 16 * m, g, hp);
-      }
-      const f32x4 z4 = unpack4(zp[m % 2]), n4 = unpack4(np[m % 2]);
-      const f32x4 h4 = unpack4(hp[m % 2]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float dn = gg[j] * (1.f - z4[j]);
-        const float dz = gg[j] * (h4[j] - n4[j]);
-        dacc[m][j] = gg[j] * z4[j];
-        nv[4 * (m % 2) + j] = dn * (1.f - n4[j] * n4[j]);
-        zv[4 * (m % 2) + j] = dz * z4[j] * (1.f - z4[j]);
-      }
-      if (m % 2 == 1) {
-        gf[2][m / 2] = pack8<S>(nv);
-        gf[1][m / 2] = pack8<S>(zv);
-        // G^'s z, n columns of tiles m - 1, m (the fragments hold them packed as bf16)
-        const u32x4 pz = __builtin_bit_cast(u32x4, gf[1][m / 2]), pn = __builtin_bit_cast(u32x4, gf[2][m / 2]);
-        store_tiles16(gh + H + 32 * (m / 2), u32x2{pz[0], pz[1]}, u32x2{pz[2], pz[3]}, g);
-        store_tiles16(gh + 2 * H + 32 * (m / 2), u32x2{pn[0], pn[1]}, u32x2{pn[2], pn[3]}, g);
-      }
-    }
-  }
-
-#pragma unroll
-  for (int round = 0; round < P1R; ++round) {
-    store_p1(round);
-    if (round + 1 < P1R) load_p1(round + 1);
   }
   __syncthreads();
-  // Pass 2's first block, in flight during pass 1.
-  load_blk(2, 0);
-
-  // Pass 1: blocks m = 0 .. MTL-1 of U_n (unrolled: static register indices).
-  float rv[8];
-  u32x2 rp[2], hq[2];   // tiles m, m + 1 of r and h (16-byte loads)
+  auto frag_of = [&](int arr, int t, int kk) __attribute__((always_inline)) {
+    return load8(&fr[arr][t][kk][lane * 8]);
+  };
+  bf16x8 w3[2][5][2];
+  {
+    f32x4 qa[2][NTL];
 #pragma unroll
-  for (int m = 0; m < MTL; ++m) {
-    if (valid) {
-      if (m % 2 == 0) {
-        load_tiles16(sv + 16 * m, g, rp);
-        load_tiles16(h + (size_t)node * H + 16 * m, g, hq);
-      }
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) mma(acc, load_fragi<S>(lds_all + m * U1 * 8, kk, lane), gf[2][kk]);
-      const int f = 16 * m + 4 * g;
-      const f32x4 r4 = unpack4(rp[m % 2]), h4 = unpack4(hq[m % 2]);
-      float rloc[4];
+      for (int t = 0; t < NTL; ++t) qa[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        rloc[j] = acc[j] * h4[j] * r4[j] * (1.f - r4[j]);
-        dacc[m][j] += acc[j] * r4[j];
+    for (int kk = 0; kk < KS; ++kk) {
+      if (kk + 1 < KS) {
+        load_w(0, kk + 1, w[(kk + 1) & 1]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) load_w(1 + c, 0, w3[0][c]);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) rv[4 * (m % 2) + j] = rloc[j];
-      if (m % 2 == 1) {
-        gf[0][m / 2] = pack8<S>(rv);
-        const u32x4 pr = __builtin_bit_cast(u32x4, gf[0][m / 2]);   // G^'s r columns of tiles m - 1, m
-        store_tiles16(gh + 32 * (m / 2), u32x2{pr[0], pr[1]}, u32x2{pr[2], pr[3]}, g);
+      for (int t = 0; t < NTL; ++t) {
+        const bf16x8 f = frag_of(2, t, kk);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) mma(qa[i][t], w[kk & 1][i], f);
       }
     }
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      float r[8], hv[8], rh[8];
+      unpack8(rraw[t], r);
+      unpack8(hraw[t], hv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float qq = qa[e & 1][t][e >> 1];
+        rh[e] = qq * hv[e] * r[e] * (1.f - r[e]);
+        acc[e & 1][t][e >> 1] += qq * r[e];
+      }
+      const bf16x8 pr = pack8<bf16s>(rh);
+      *reinterpret_cast<bf16x8*>(&fr[0][t][fw][lane * 8]) = pr;
+      if (node_of(t) < n_pad) *reinterpret_cast<bf16x8*>(ghat + (size_t)node_of(t) * 3 * H + fe) = pr;
+    }
   }
-  // Every wave is done with U_n before pass 2's buffers overwrite it.
   __syncthreads();
-  // Pass 2: blocks n = 0 .. MTL-1 of Wi (da) and U_r, U_z (dh).
+  f32x4 da[2][NTL];
 #pragma unroll
-  for (int n = 0; n < MTL; ++n) {
-    const int b = n & 1;
-    store_blk(2, b);
-    __syncthreads();
-    if (n + 1 < MTL) load_blk(2, n + 1);
-    if (valid) {
-      f32x4 da = {0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int gate = 0; gate < 3; ++gate)
+    for (int t = 0; t < NTL; ++t) da[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) mma(da, gf[gate][kk], load_fragi<S>(lw[b], gate * KS + kk, lane));
-      store4(daT + (size_t)(16 * n + q) * n_pad + n0 + 4 * g, da[0], da[1], da[2], da[3]);
-      f32x4 d = dacc[n];
+  for (int kk = 0; kk < KS; ++kk) {
+    if (kk + 1 < KS) {
 #pragma unroll
-      for (int gate = 0; gate < 2; ++gate)
+      for (int c = 0; c < 5; ++c) load_w(1 + c, kk + 1, w3[(kk + 1) & 1][c]);
+    }
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) mma(d, load_fragi<S>(lw[b] + BLK_W, gate * KS + kk, lane), gf[gate][kk]);
-      store4(dh + (size_t)node * H + 16 * n + 4 * g, d[0], d[1], d[2], d[3]);
+    for (int t = 0; t < NTL; ++t) {
+      const bf16x8 f[3] = {frag_of(0, t, kk), frag_of(1, t, kk), frag_of(2, t, kk)};
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          mma(da[i][t], f[c], w3[kk & 1][c][i]);
+          if (c < 2) mma(acc[i][t], w3[kk & 1][3 + c][i], f[c]);
+        }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NTL; t += 2) {
+    if (n0 + 16 * t >= n_pad) continue;   // n_pad is a multiple of 32: the pair is in or out
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float v[8] = {da[i][t][0], da[i][t][1], da[i][t][2], da[i][t][3],
+                          da[i][t + 1][0], da[i][t + 1][1], da[i][t + 1][2], da[i][t + 1][3]};
+      *reinterpret_cast<bf16x8*>(daT + (size_t)(32 * fw + 2 * q + i) * n_pad + n0 + 16 * t + 8 * g) = pack8<bf16s>(v);
+    }
+#pragma unroll
+    for (int u = t; u < t + 2; ++u) {
+      float* row = dh + (size_t)node_of(u) * H + fe;
+      *reinterpret_cast<f32x4*>(row) = f32x4{acc[0][u][0], acc[1][u][0], acc[0][u][1], acc[1][u][1]};
+      *reinterpret_cast<f32x4*>(row + 4) = f32x4{acc[0][u][2], acc[1][u][2], acc[0][u][3], acc[1][u][3]};
     }
   }
 }
@@ -940,7 +878,7 @@ constexpr bool gru_big() {
 template <typename S, int H>
 hipError_t gru_pack_h(const void* Wi, const void* U, void* packed, hipStream_t st) {
   if constexpr (gru_big<S, H>()) {
-    const int units = 2 * dev::GruPack<H>::UNITS;
+    const int units = 2 * dev::gru_pack_units(H);
     hipLaunchKernelGGL((dev::gru_pack_kernel<S, H>), dim3((units + 255) / 256), dim3(256), 0, st,
                        static_cast<const S*>(Wi), static_cast<const S*>(U), static_cast<S*>(packed));
     return hipGetLastError();
@@ -990,24 +928,34 @@ hipError_t gru_bwd_nodes_h(int n_pad, const float* dh_out, const void* h, const 
                            const void* U, void* da, float* dh, void* ghat, const void* packed, hipStream_t st) {
   if constexpr (gru_big<S, H>()) {
     // the reverse region follows the forward one
-    const S* pk = packed ? static_cast<const S*>(packed) + (size_t)dev::GruPack<H>::UNITS * 8 : nullptr;
-#define GGNN_GRU_BWD_BIG(PK)                                                                                   \
-  hipLaunchKernelGGL((dev::gru_bwd_big_kernel<S, H, PK>), dim3((n_pad + 127) / 128), dim3(512), 0, st, dh_out, \
-                     static_cast<const S*>(h), static_cast<const S*>(saved), static_cast<const S*>(Wi),         \
-                     static_cast<const S*>(U), pk, static_cast<S*>(da), dh, static_cast<S*>(ghat), n_pad)
-    if (pk != nullptr)
-      GGNN_GRU_BWD_BIG(true);
+    const S* pk = packed ? static_cast<const S*>(packed) + (size_t)dev::gru_pack_units(H) * 8 : nullptr;
+#define GGNN_GRU_BWD_COLS(NTL, PK)                                                                                \
+  hipLaunchKernelGGL((dev::gru_bwd_cols_kernel<H, NTL, PK>), dim3((n_pad + 16 * NTL - 1) / (16 * NTL)),           \
+                     dim3(H / 32 * 64), 0, st, dh_out, static_cast<const S*>(h), static_cast<const S*>(saved),    \
+                     static_cast<const S*>(Wi), static_cast<const S*>(U), pk, static_cast<S*>(da), dh,            \
+                     static_cast<S*>(ghat), n_pad)
+    // 32 nodes per workgroup on small grids, else 64, so that the weights are read less often (whole reverse with
+    // the weight gradients, H = 256: 70 us against 77 at 8,192 nodes, 104 against 84 at 12,352; H = 128: 29 / 31 and
+    // 39 / 35).
+    const bool small = n_pad <= 8192;
+    if (small && pk != nullptr)
+      GGNN_GRU_BWD_COLS(2, true);
+    else if (small)
+      GGNN_GRU_BWD_COLS(2, false);
+    else if (pk != nullptr)
+      GGNN_GRU_BWD_COLS(4, true);
     else
-      GGNN_GRU_BWD_BIG(false);
-#undef GGNN_GRU_BWD_BIG
+      GGNN_GRU_BWD_COLS(4, false);
+#undef GGNN_GRU_BWD_COLS
     return hipGetLastError();
-  }
-  constexpr int WAVES = 4;
-  hipLaunchKernelGGL((dev::gru_bwd_kernel<S, H, WAVES>), dim3((n_pad + 16 * WAVES - 1) / (16 * WAVES)),
+  } else {
+    constexpr int WAVES = 4;
+    hipLaunchKernelGGL((dev::gru_bwd_kernel<S, H, WAVES>), dim3((n_pad + 16 * WAVES - 1) / (16 * WAVES)),
                      dim3(WAVES * 64), 0, st, dh_out, static_cast<const S*>(h), static_cast<const S*>(saved),
                      static_cast<const S*>(Wi), static_cast<const S*>(U), static_cast<S*>(da), dh,
                      static_cast<S*>(ghat), n_pad);
-  return hipGetLastError();
+    return hipGetLastError();
+  }
 }
 
 template <typename S, int H>

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_helpers import say, dev, host, round_to, torch_dt
+from gpu_helpers import TOL, relerr, say, dev, host, round_to, torch_dt
 
 pytestmark = pytest.mark.gpu
 
@@ -191,3 +191,29 @@ def test_parameters_keep_their_addresses(dt):
     for v in m._views(used):
         v.fill_(True)
     assert not m.master[~used].any() and not m.velocity[~used].any()
+
+
+# bf16 node reverse at H >= 128: 32 nodes per workgroup up to 8,192 nodes, else 64, the last workgroup partly past the
+# end; the upstream gradient's buffer taking dh is what the pass over several steps does.
+@pytest.mark.parametrize("H,n", [(128, 32), (128, 96), (128, 8192), (128, 8224), (256, 32), (256, 8224)])
+def test_gru_update_bwd_forms(H, n):
+    say(f"gru_update_bwd form H={H} n={n}")
+    rng = np.random.default_rng(H + n)
+    k = 1 / np.sqrt(H)
+    a = round_to("f32", rng.standard_normal((n, H)))
+    h = round_to("bf16", rng.standard_normal((n, H)))
+    Wi, U = (round_to("bf16", rng.uniform(-k, k, (H, 3 * H))) for _ in range(2))
+    b = round_to("f32", rng.uniform(-k, k, 3 * H))
+    g = round_to("f32", rng.standard_normal((n, H)))
+    gates = [round_to("bf16", x) for x in O.gru_forward(a, h, Wi, U, b)[1:]]
+    want = O.gru_backward(g, a, h, *gates, Wi, U)
+    ws_n = capi.ggnn_gru_update_bwd_workspace_bytes("bf16", n, H)
+    ws = torch.empty(ws_n, dtype=torch.uint8, device="cuda")
+    da = torch.full((H, n), float("nan"), device="cuda", dtype=torch.bfloat16)
+    dh = torch.full((n, H), float("nan"), device="cuda")
+    dWi, dU, db = torch.zeros((H, 3 * H), device="cuda"), torch.zeros((H, 3 * H), device="cuda"), torch.zeros(3 * H, device="cuda")
+    capi.ggnn_gru_update_bwd("bf16", n, H, dev(g), dev(a), dev(h, "bf16"), dev(np.concatenate(gates, 1), "bf16"),
+                             dev(Wi, "bf16"), dev(U, "bf16"), da, dh, dWi, dU, db, ws, ws_n)
+    got = (host(da).T, host(dh), host(dWi), host(dU), host(db))
+    for w, x in zip(want, got):
+        assert relerr(x, w) <= TOL["bf16"]
