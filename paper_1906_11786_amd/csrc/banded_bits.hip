@@ -177,6 +177,7 @@ struct BitsCfg {
   // Stage the three neighbouring node blocks once per workgroup when they fit
   // in 64 KB; otherwise stream KC-node chunks per edge type.
   static constexpr bool ALL = 3 * H * (B + V) * (int)sizeof(S) <= 65536;
+  static constexpr bool WDIR_ = ALL && H <= 64;
   static constexpr int KC = ALL ? B : (B < 64 ? B : 64);
   static constexpr int NBUF = ALL ? 3 : 1;
   static constexpr int VP = KC + V;
@@ -194,11 +195,15 @@ struct BitsCfg {
   // the bf16 forms with H = 256 keep at least two waves (their one-wave
   // forms are not built: the code generator fails on them).
   static constexpr int MINW = ((sizeof(S) == 4 && H >= 128) || H >= 256) && B / RPW >= 2 ? 2 : 1;
+  // Step kernel forms that are launched: bf16 with the blocks staged whole
+  // and direct weights, and the streamed forward at H = 256 up to B = 256.
+  static constexpr bool FWD = sizeof(S) == 2 && (WDIR_ || (H == 256 && B <= 256));
+  static constexpr bool REV = sizeof(S) == 2 && WDIR_;
   // Forward, H <= 64 with the blocks staged: the transform's weight
   // fragments are read straight from global memory (L1/L2 resident, issued
   // at the top of each type and used at its end), so no weight staging sits
   // in the prologue and the type loop has no barrier.
-  static constexpr bool WDIR = ALL && H <= 64;
+  static constexpr bool WDIR = WDIR_;
   static constexpr int WP = H + V;          // W^T row pitch (LDS chunks otherwise)
 };
 
@@ -258,9 +263,6 @@ struct BitsCfg {
 #ifndef GGNN_BITS_GW_TG0
 #define GGNN_BITS_GW_TG0 0
 #endif
-#ifndef GGNN_BITS_DM_LDS
-#define GGNN_BITS_DM_LDS 1
-#endif
 constexpr int kSnFused = 32;   // supernodes handled inside the fused step kernels
 template <typename S, int H, int B, int WAVES, bool WDIR, int TG, bool REV, bool GRU, bool SN = false>
 __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
@@ -278,7 +280,9 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
   constexpr int WC = WDIR ? H : (H < 64 ? H : 64);   // weight rows per chunk
   constexpr int NP = (sizeof(S) == 2 && !REV) ? 2 : 1;
   constexpr int ROWB = B / 8;
+  static_assert(sizeof(S) == 2, "fp32 steps run in banded_direct.hip");
   static_assert(!WDIR || C::WDIR, "direct weights need the staged blocks and H <= 64");
+  static_assert(WDIR || !REV, "blocks streamed per type: the forward only");
   static_assert(TG == 1 || WDIR, "type groups need the barrier-free loop");
   static_assert(TG == 1 || (TG - 1) * WAVES * kWave * NTW * MT * 16 <= (int)(C::NBUF * H * VP * sizeof(S)),
                 "partial sums must fit in the staged-block space");
@@ -292,11 +296,10 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
   // and, per type group, the record rows of the wave holding nodes 0..31
   // (NTW x MT 1 KB copies, one 16-byte unit per lane each).
   __shared__ __attribute__((aligned(16))) S hubw[SN ? kSnFused * H : 8];
-  // reverse, bf16 with the blocks staged: each wave's dM tile (RPW rows,
+  // reverse: each wave's dM tile (RPW rows,
   // pitch DMP), for row-ordered stores
-  constexpr bool DMS = REV && C::ALL && sizeof(S) == 2 && GGNN_BITS_DM_LDS;
   constexpr int DMP = H + 8;
-  __shared__ __attribute__((aligned(16))) S dms[DMS ? TG * WAVES * C::RPW * DMP : 8];
+  __shared__ __attribute__((aligned(16))) S dms[REV ? TG * WAVES * C::RPW * DMP : 8];
   __shared__ __attribute__((aligned(1024))) float recb[SN ? TG * NTW * MT * 256 : 4];
 
   const int nb = n_pad / B;
@@ -511,25 +514,19 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
           } else {
             // column 16mo + q of W_e, rows 32kk + 8g + 0..7 (2-byte gathers)
             const S* p = we + (size_t)(32 * kk + 8 * g) * H + 16 * mo + q;
-            if constexpr (sizeof(S) == 2) {
-              u32x4 w;
+            u32x4 w;
 #pragma unroll
-              for (int d = 0; d < 4; ++d)
-                w[d] = static_cast<uint32_t>(p[(size_t)(2 * d) * H]) |
-                       (static_cast<uint32_t>(p[(size_t)(2 * d + 1) * H]) << 16);
-              wf[mo][kk] = __builtin_bit_cast(bf16x8, w);
-            } else {
-#pragma unroll
-              for (int x = 0; x < 8; ++x) wf[mo][kk][x] = p[(size_t)x * H];
-            }
+            for (int d = 0; d < 4; ++d)
+              w[d] = static_cast<uint32_t>(p[(size_t)(2 * d) * H]) |
+                     (static_cast<uint32_t>(p[(size_t)(2 * d + 1) * H]) << 16);
+            wf[mo][kk] = __builtin_bit_cast(bf16x8, w);
           }
         }
     }
   };
 
   // Per-type weight chunks in LDS (not WDIR): chunk rows o in [oc, oc + WC),
-  // wt[o][h] = W[e][h][oc + o] (forward, transposed on the write) or
-  // W[e][oc + o][h] (reverse, plain copies); H * WC / V 16-byte units,
+  // wt[o][h] = W[e][h][oc + o], transposed on the write; H * WC / V 16-byte units,
   // prefetched into registers during the aggregation.
   constexpr int WU = WDIR ? 1 : (H * (WC / V) + NT - 1) / NT;
   u32x4 wreg[WU];
@@ -538,13 +535,8 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
     for (int u = 0; u < WU; ++u) {
       const int lin = u * NT + tid;
       if ((H * (WC / V)) % NT == 0 || lin < H * (WC / V)) {
-        if constexpr (REV) {
-          const int o = lin / (H / V), h8 = (lin % (H / V)) * V;
-          wreg[u] = *reinterpret_cast<const u32x4*>(W + (size_t)e * H * H + (size_t)(oc + o) * H + h8);
-        } else {
-          const int h = lin / (WC / V), o8 = (lin % (WC / V)) * V;
-          wreg[u] = *reinterpret_cast<const u32x4*>(W + (size_t)e * H * H + (size_t)h * H + oc + o8);
-        }
+        const int h = lin / (WC / V), o8 = (lin % (WC / V)) * V;
+        wreg[u] = *reinterpret_cast<const u32x4*>(W + (size_t)e * H * H + (size_t)h * H + oc + o8);
       }
     }
   };
@@ -553,15 +545,10 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
     for (int u = 0; u < WU; ++u) {
       const int lin = u * NT + tid;
       if ((H * (WC / V)) % NT == 0 || lin < H * (WC / V)) {
-        if constexpr (REV) {
-          const int o = lin / (H / V), h8 = (lin % (H / V)) * V;
-          *reinterpret_cast<u32x4*>(&wt[o * WP + h8]) = wreg[u];
-        } else {
-          const int h = lin / (WC / V), o8 = (lin % (WC / V)) * V;
-          const S* pw = reinterpret_cast<const S*>(&wreg[u]);
+        const int h = lin / (WC / V), o8 = (lin % (WC / V)) * V;
+        const S* pw = reinterpret_cast<const S*>(&wreg[u]);
 #pragma unroll
-          for (int x = 0; x < V; ++x) wt[(o8 + x) * WP + h] = pw[x];
-        }
+        for (int x = 0; x < V; ++x) wt[(o8 + x) * WP + h] = pw[x];
       }
     }
   };
@@ -647,11 +634,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
       for (int c0 = 0; c0 < B; c0 += KC) {
         if constexpr (!C::ALL) {
           __syncthreads();
-          if constexpr (REV) {
-            stage_cols<S, H, KC, VP, NT, C::ROWS, true>(vt[0], X, n_pad, (k - 1 + s) * B + c0, tid);
-          } else {
-            stage_nodes_T<S, H, KC, VP, NT, C::ROWS>(vt[0], X, (k - 1 + s) * B + c0, tid);
-          }
+          stage_nodes_T<S, H, KC, VP, NT, C::ROWS>(vt[0], X, (k - 1 + s) * B + c0, tid);
           __syncthreads();
         }
         const S* v = vt[C::ALL ? s : 0];
@@ -740,7 +723,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
           pf[0][n][kk] = pack8<S>(v8);
         }
       }
-    if constexpr (REV && DMS) {
+    if constexpr (REV) {
       // dM_e rows of this wave's nodes through the wave's LDS tile: written
       // as the lanes hold them (node 16n + q, features 32kk + 8g .. + 7),
       // read back in row order, so that each store covers 1 KB of
@@ -758,23 +741,6 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
         const int u = i * kWave + lane;   // 16-byte unit u of the wave's rows: row u / (H / 8)
         const int r = u / (H / 8), c = (u % (H / 8)) * 8;
         *reinterpret_cast<u32x4*>(rows0 + (size_t)r * H + c) = *reinterpret_cast<const u32x4*>(dt + r * DMP + c);
-      }
-    } else if constexpr (REV) {
-      // dM_e rows of this wave's nodes (node-major, rows of type e start at
-      // row e * ldm): features 32kk + 8g .. 32kk + 8g + 7 (rev_row order).
-#pragma unroll
-      for (int n = 0; n < NTW; ++n) {
-        S* row = dM + ((size_t)e * ldm + k * B + rw + 16 * n + q) * H + 4 * g;
-#pragma unroll
-        for (int kk = 0; kk < HK; ++kk) {
-          if constexpr (sizeof(S) == 2) {
-            *reinterpret_cast<u32x4*>(row + 32 * kk + 4 * g) = __builtin_bit_cast(u32x4, pf[0][n][kk]);
-          } else {
-            const f32x8 w = pf[0][n][kk];
-            *reinterpret_cast<f32x4*>(row + 32 * kk + 4 * g) = f32x4{w[0], w[1], w[2], w[3]};
-            *reinterpret_cast<f32x4*>(row + 32 * kk + 4 * g + 4) = f32x4{w[4], w[5], w[6], w[7]};
-          }
-        }
       }
     }
     if constexpr (WDIR) {
@@ -832,21 +798,15 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
   }
   // Epilogue operands of this wave's tile requested now, in flight across
   // the barriers: h (forward) or the gates of the previous step (reverse).
-  // h as raw 16-byte units in bf16 (features 32kk + 8g.., split at use:
-  // split_tiles16), as fragments in fp32.
-  constexpr bool HRAW = sizeof(S) == 2;
-  frag_t<S> hf_pre[(GRU && !REV && SPLIT && !HRAW) ? H / 32 : 1];
-  u32x4 hraw_pre[(GRU && !REV && SPLIT && HRAW) ? H / 32 : 1];
+  // h as raw 16-byte units (features 32kk + 8g.., split at use: split_tiles16).
+  u32x4 hraw_pre[(GRU && !REV && SPLIT) ? H / 32 : 1];
   GruBwdIn<S, H> gin_pre;
   if constexpr (GRU && SPLIT) {
     const int node = k * B + rw + 16 * tg + q;
     if constexpr (!REV) {
 #pragma unroll
       for (int kk = 0; kk < H / 32; ++kk) {
-        if constexpr (HRAW)
-          hraw_pre[kk] = *reinterpret_cast<const u32x4*>(X + (size_t)node * H + 32 * kk + 8 * g);
-        else
-          hf_pre[kk] = rowfrag<S>(X + (size_t)node * H, kk, g);
+        hraw_pre[kk] = *reinterpret_cast<const u32x4*>(X + (size_t)node * H + 32 * kk + 8 * g);
       }
     } else {
       gin_pre.load(rh_saved, rh_h, node, g);
@@ -940,17 +900,11 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
         } else {
           af[0][kk] = pack8<S>(v8);
         }
-        if constexpr (HRAW) {
-          const u32x4 raw =
-              SPLIT ? hraw_pre[kk] : *reinterpret_cast<const u32x4*>(X + (size_t)node * H + 32 * kk + 8 * g);
-          u32x2 t[2];
-          split_tiles16(raw, t);
-          hf[kk] = __builtin_bit_cast(frag_t<S>, u32x4{t[0][0], t[0][1], t[1][0], t[1][1]});
-        } else if constexpr (SPLIT) {
-          hf[kk] = hf_pre[kk];
-        } else {
-          hf[kk] = rowfrag<S>(X + (size_t)node * H, kk, g);
-        }
+        const u32x4 raw =
+            SPLIT ? hraw_pre[kk] : *reinterpret_cast<const u32x4*>(X + (size_t)node * H + 32 * kk + 8 * g);
+        u32x2 t[2];
+        split_tiles16(raw, t);
+        hf[kk] = __builtin_bit_cast(frag_t<S>, u32x4{t[0][0], t[0][1], t[1][0], t[1][1]});
       }
       // Weight fragments of gate columns 16*t16 .. 16*t16 + 15 (fragment order).
       auto gfrag = [&](int mat, int t16, int kk) __attribute__((always_inline)) {
@@ -982,13 +936,10 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
             rv[4 * p + j] = sigmoidf_(ar[2 * c2 + p][j] + bg[f + j]);
             rhv[4 * p + j] = rv[4 * p + j] * static_cast<float>(hf[c2][4 * p + j]);
           }
-          if constexpr (!HRAW)
-            store4(saved + (size_t)node * 3 * H + f, rv[4 * p], rv[4 * p + 1], rv[4 * p + 2], rv[4 * p + 3]);
         }
-        if constexpr (HRAW) {   // r of the two tiles as one 16-byte store per lane
-          const u32x4 pr = __builtin_bit_cast(u32x4, pack8<S>(rv));
-          store_tiles16(saved + (size_t)node * 3 * H + 32 * c2, u32x2{pr[0], pr[1]}, u32x2{pr[2], pr[3]}, g);
-        }
+        // r of the two tiles as one 16-byte store per lane
+        const u32x4 pr = __builtin_bit_cast(u32x4, pack8<S>(rv));
+        store_tiles16(saved + (size_t)node * 3 * H + 32 * c2, u32x2{pr[0], pr[1]}, u32x2{pr[2], pr[3]}, g);
         rh[c2] = pack8<S>(rhv);
       }
       // z, n and the new state (2 NC independent chains).
@@ -1026,20 +977,13 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_bits_kernel(
           nk[4 * (c % 2) + j] = nn[j];
           ok[4 * (c % 2) + j] = o[j];
         }
-        if constexpr (HRAW) {
-          if (c % 2 == 1) {   // h', z, n of tiles c - 1, c as 16-byte stores
-            const u32x4 po = __builtin_bit_cast(u32x4, pack8<S>(ok)), pz = __builtin_bit_cast(u32x4, pack8<S>(zk)),
-                        pn = __builtin_bit_cast(u32x4, pack8<S>(nk));
-            store_tiles16(h_out + (size_t)node * H + 32 * (c / 2), u32x2{po[0], po[1]}, u32x2{po[2], po[3]}, g);
-            store_tiles16(saved + (size_t)node * 3 * H + H + 32 * (c / 2), u32x2{pz[0], pz[1]}, u32x2{pz[2], pz[3]},
-                          g);
-            store_tiles16(saved + (size_t)node * 3 * H + 2 * H + 32 * (c / 2), u32x2{pn[0], pn[1]},
-                          u32x2{pn[2], pn[3]}, g);
-          }
-        } else {
-          store4(h_out + (size_t)node * H + f, o[0], o[1], o[2], o[3]);
-          store4(saved + (size_t)node * 3 * H + H + f, z[0], z[1], z[2], z[3]);
-          store4(saved + (size_t)node * 3 * H + 2 * H + f, nn[0], nn[1], nn[2], nn[3]);
+        if (c % 2 == 1) {   // h', z, n of tiles c - 1, c as 16-byte stores
+          const u32x4 po = __builtin_bit_cast(u32x4, pack8<S>(ok)), pz = __builtin_bit_cast(u32x4, pack8<S>(zk)),
+                      pn = __builtin_bit_cast(u32x4, pack8<S>(nk));
+          store_tiles16(h_out + (size_t)node * H + 32 * (c / 2), u32x2{po[0], po[1]}, u32x2{po[2], po[3]}, g);
+          store_tiles16(saved + (size_t)node * 3 * H + H + 32 * (c / 2), u32x2{pz[0], pz[1]}, u32x2{pz[2], pz[3]}, g);
+          store_tiles16(saved + (size_t)node * 3 * H + 2 * H + 32 * (c / 2), u32x2{pn[0], pn[1]}, u32x2{pn[2], pn[3]},
+                        g);
         }
       }
     }
@@ -1279,6 +1223,7 @@ BitsPlan bits_plan(int mode, int n_pad, int E) {
 template <typename S, int H, int B>
 hipError_t bits_launch(const BitsArgs& A, hipStream_t st) {
   using C = dev::BitsCfg<S, H, B>;
+  if ((A.mode == 0 && !C::FWD) || (A.mode == 1 && !C::REV)) return hipErrorNotSupported;   // another kernel's sizes
   const BitsPlan plan = bits_plan<S, H, B>(A.mode, A.n_pad, A.E);
   const int waves = plan.waves, groups = plan.groups, blocks = plan.blocks;
   const bool tg2 = plan.tg2;
@@ -1318,29 +1263,33 @@ hipError_t bits_launch(const BitsArgs& A, hipStream_t st) {
     }                                                                                                         \
     GGNN_STEP_SN(WV, TGN, REVB, GRUB, false);                                                                 \
   } while (0)
-#define GGNN_BITS_CASE(WV)                                                                                   \
-  case WV:                                                                                                   \
-    if constexpr (B / C::RPW >= WV && WV >= C::MINW && (WV <= 4 || (!C::ALL && H >= 256))) {         \
-      if (A.mode == 0 && gru)                                                                                \
-        GGNN_STEP(WV, (C::WDIR ? 2 : 1), false, C::WDIR);                                                    \
-      else if (A.mode == 0 && tg2)                                                                           \
-        GGNN_STEP(WV, (C::WDIR ? 2 : 1), false, false);                                                      \
-      else if (A.mode == 0)                                                                                  \
-        GGNN_STEP(WV, 1, false, false);                                                                      \
-      else {                                                                                                 \
-        if constexpr (WV <= 4) { /* eight-wave forms: forward only */                                       \
-          if (A.mode == 1 && rgru)                                                                           \
-            GGNN_STEP(WV, (C::WDIR ? 2 : 1), true, C::WDIR);                                                 \
-          else if (A.mode == 1 && tg2)                                                                       \
-            GGNN_STEP(WV, (C::WDIR ? 2 : 1), true, false);                                                   \
-          else if (A.mode == 1)                                                                              \
-            GGNN_STEP(WV, 1, true, false);                                                                   \
-          else                                                                                               \
-            hipLaunchKernelGGL((dev::bits_bwd_kernel<S, H, B, WV>), dim3(blocks), dim3(WV * 64), 0, st, bp,  \
-                               vp, static_cast<S*>(A.out), A.n_pad, A.E, groups, A.ldm);                     \
-        }                                                                                                    \
-      }                                                                                                      \
-    }                                                                                                        \
+#define GGNN_BITS_CASE(WV)                                                                                          \
+  case WV:                                                                                                          \
+    if constexpr (B / C::RPW >= WV && WV >= C::MINW && (WV <= 4 || (!C::ALL && H >= 256))) {                        \
+      if (A.mode == 0) {                                                                                            \
+        if constexpr (C::FWD) {                                                                                     \
+          if (gru)                                                                                                  \
+            GGNN_STEP(WV, (C::WDIR ? 2 : 1), false, C::WDIR);                                                       \
+          else if (tg2)                                                                                             \
+            GGNN_STEP(WV, (C::WDIR ? 2 : 1), false, false);                                                         \
+          else                                                                                                      \
+            GGNN_STEP(WV, 1, false, false);                                                                         \
+        }                                                                                                           \
+      } else if (A.mode == 1) {                                                                                     \
+        if constexpr (C::REV && WV <= 4) {                                                                          \
+          if (rgru)                                                                                                 \
+            GGNN_STEP(WV, 2, true, true);                                                                           \
+          else if (tg2)                                                                                             \
+            GGNN_STEP(WV, 2, true, false);                                                                          \
+          else                                                                                                      \
+            GGNN_STEP(WV, 1, true, false);                                                                          \
+        }                                                                                                           \
+      } else {                                                                                                      \
+        if constexpr (WV <= 4) /* eight-wave forms: forward only */                                                 \
+          hipLaunchKernelGGL((dev::bits_bwd_kernel<S, H, B, WV>), dim3(blocks), dim3(WV * 64), 0, st, bp, vp,       \
+                             static_cast<S*>(A.out), A.n_pad, A.E, groups, A.ldm);                                  \
+      }                                                                                                             \
+    }                                                                                                               \
     break;
   switch (waves) {
     GGNN_BITS_CASE(8)
@@ -1379,6 +1328,7 @@ hipError_t bits_t(int H, int B, const BitsArgs& A, hipStream_t st) {
 }  // namespace
 
 namespace GGNN_IMPL_NS {
+#if GGNN_DT_BF16
 hipError_t launch_step_fwd_bits(int n_pad, int B, int H, int E, const void* bits, const void* X, const void* W,
                                 const float* bias, float* a, hipStream_t st) {
   return bits_t<dev::dt_t>(H, B, BitsArgs{0, bits, X, W, bias, a, nullptr, nullptr, 0, n_pad, E}, st);
@@ -1396,15 +1346,6 @@ hipError_t launch_step_fwd_bits_gru(int n_pad, int B, int H, int E, const void* 
   A.saved = saved;
   A.fused_gru = fused;
   return bits_t<dev::dt_t>(H, B, A, st);
-}
-
-hipError_t launch_transpose_weights(int H, int E, const void* W, void* Wt, hipStream_t st) {
-  using S = dev::dt_t;
-  constexpr int V = 16 / sizeof(S);
-  const long n = (long)E * (H / V) * (H / V);
-  hipLaunchKernelGGL((dev::transpose_weights_kernel<S>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     static_cast<const S*>(W), static_cast<S*>(Wt), H, E);
-  return hipGetLastError();
 }
 
 hipError_t launch_step_bwd_bits(int n_pad, int B, int H, int E, const void* bits_t_, const void* da, const void* W,
@@ -1426,6 +1367,16 @@ hipError_t launch_step_bwd_bits_gru(int n_pad, int B, int H, int E, const void* 
   A.rh_ghat = ghat_prev;
   A.fused_gru = fused;
   return bits_t<dev::dt_t>(H, B, A, st);
+}
+#endif
+
+hipError_t launch_transpose_weights(int H, int E, const void* W, void* Wt, hipStream_t st) {
+  using S = dev::dt_t;
+  constexpr int V = 16 / sizeof(S);
+  const long n = (long)E * (H / V) * (H / V);
+  hipLaunchKernelGGL((dev::transpose_weights_kernel<S>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                     static_cast<const S*>(W), static_cast<S*>(Wt), H, E);
+  return hipGetLastError();
 }
 
 hipError_t launch_banded_bwd_bits(int n_pad, int B, int H, int E, const void* bits_t_, const void* da, void* dM,

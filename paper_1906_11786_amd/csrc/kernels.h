@@ -62,23 +62,9 @@ struct SnStep {
                                hipStream_t st);                                                                   \
   hipError_t launch_banded_bwd(int n_pad, int B, int H, int E, const void* band, const void* da, void* dM,        \
                                long ldm, hipStream_t st);                                                         \
-  hipError_t launch_step_fwd_bits(int n_pad, int B, int H, int E, const void* bits, const void* X, const void* W, \
-                                  const float* bias, float* a, hipStream_t st);                                   \
   hipError_t launch_banded_bwd_bits(int n_pad, int B, int H, int E, const void* bits_t, const void* da, void* dM, \
                                     long ldm, hipStream_t st);                                                    \
-  hipError_t launch_step_fwd_bits_gru(int n_pad, int B, int H, int E, const void* bits, const void* X,           \
-                                      const void* W, const void* Wt, const float* bias, float* a, const void* Wi, \
-                                      const void* U, const float* bg, void* h_out, void* saved, bool* fused,      \
-                                      hipStream_t st);                                                            \
   hipError_t launch_transpose_weights(int H, int E, const void* W, void* Wt, hipStream_t st);                    \
-  hipError_t launch_step_bwd_bits_gru(int n_pad, int B, int H, int E, const void* bits_t, const void* da,         \
-                                      const void* W, const float* dX_in, float* dX_out, void* dM, long ldm,       \
-                                      const void* Wi, const void* U, const void* h_prev, const void* saved_prev,  \
-                                      void* da_prev, float* dh_prev, void* ghat_prev, bool* fused,                \
-                                      hipStream_t st);                                                            \
-  hipError_t launch_step_bwd_bits(int n_pad, int B, int H, int E, const void* bits_t, const void* da,             \
-                                  const void* W, const float* dX_in, float* dX_out, void* dM, long ldm,           \
-                                  hipStream_t st);                                                                \
   hipError_t launch_transform_fwd(int n_pad, int H, int E, const void* X, const void* W, const float* bias,       \
                                   float* M, hipStream_t st);                                                      \
   hipError_t launch_transform_bwd_dx(int n_pad, int H, int E, const void* W, const void* dM, long ld,             \
@@ -118,6 +104,21 @@ struct SnStep {
 
 namespace impl_bf16 {
 GGNN_DT_LAUNCHERS
+// The narrow step kernel (csrc/banded_bits.hip).
+hipError_t launch_step_fwd_bits(int n_pad, int B, int H, int E, const void* bits, const void* X, const void* W,
+                                const float* bias, float* a, hipStream_t st);
+hipError_t launch_step_fwd_bits_gru(int n_pad, int B, int H, int E, const void* bits, const void* X,
+                                    const void* W, const void* Wt, const float* bias, float* a, const void* Wi,
+                                    const void* U, const float* bg, void* h_out, void* saved, bool* fused,
+                                    hipStream_t st);
+hipError_t launch_step_bwd_bits_gru(int n_pad, int B, int H, int E, const void* bits_t, const void* da,
+                                    const void* W, const float* dX_in, float* dX_out, void* dM, long ldm,
+                                    const void* Wi, const void* U, const void* h_prev, const void* saved_prev,
+                                    void* da_prev, float* dh_prev, void* ghat_prev, bool* fused,
+                                    hipStream_t st);
+hipError_t launch_step_bwd_bits(int n_pad, int B, int H, int E, const void* bits_t, const void* da,
+                                const void* W, const float* dX_in, float* dX_out, void* dM, long ldm,
+                                hipStream_t st);
 // Fused supernode steps (bf16, H <= 64, grids small enough for the
 // two-group forms): whether both fused steps take the supernode share at
 // this size, and the forward step (with its GRU) and reverse step (with the
@@ -184,11 +185,17 @@ inline bool step_direct(int dt, int n_pad, int B, int H, bool rev) {
   if (H == 64) return B >= 256 || (rev && B >= 64 && tiles <= 128);
   return tiles <= (H == 128 || B == 512 ? 1024 : 512);
 }
+// Without the transposed weights the wide kernel does not apply, and the forward above those sizes is the direct
+// kernel at H = 128 (B = 128, 6 types, 65,536 nodes: 151 us with the narrow kernel's streamed blocks, 85 so; B = 512:
+// 320 / 189) and the narrow kernel at H = 256 (B = 256, 60,416 nodes: 492 / 902), except at B = 512 (803 / 620).
+inline bool step_direct_no_wt(int dt, int n_pad, int B, int H) {
+  return H == 128 || (H == 256 && B == 512) || step_direct(dt, n_pad, B, H, false);
+}
 
 // 1-bit band: fused aggregate-first forward and transposed-band reverse.
 inline hipError_t launch_step_fwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits, const void* X,
                                        const void* W, const float* bias, float* a, hipStream_t st) {
-  if (step_direct(dt, n_pad, B, H, false))
+  if (step_direct_no_wt(dt, n_pad, B, H))
     return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, nullptr, bias, a, nullptr, nullptr, 0,
                         st);
   return impl_bf16::launch_step_fwd_bits(n_pad, B, H, E, bits, X, W, bias, a, st);
@@ -210,7 +217,7 @@ inline hipError_t launch_step_fwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* W, const void* Wt, const float* bias, float* a,
                                            const void* Wi, const void* U, const float* bg, void* h_out, void* saved,
                                            bool* fused, hipStream_t st) {
-  if (step_direct(dt, n_pad, B, H, false)) {
+  if (Wt == nullptr ? step_direct_no_wt(dt, n_pad, B, H) : step_direct(dt, n_pad, B, H, false)) {
     if (fused) *fused = false;
     return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
   }
