@@ -290,9 +290,10 @@ ggnn_status ggnn_step_bits_gru(ggnn_dtype dt, int32_t n_pad, int32_t B, int32_t 
 ggnn_status ggnn_transpose_weights(ggnn_dtype dt, int32_t H, int32_t E, const void* W, void* Wt, void* stream);
 
 /* GRU weights repacked for the large-width GRU kernels (bf16, H = 128 or 256):
- * those kernels stream Wi and U through on-chip memory in stages, and the
- * packed copy holds every stage's 16-byte pieces in the order they are
- * staged, so staging becomes contiguous loads.  The packing is a pure
+ * those kernels read Wi and U as matrix-core fragments straight from memory,
+ * and the packed copy holds every fragment's 16-byte pieces back to back, for
+ * the forward and for the reverse, so that a fragment is one contiguous 1 KB
+ * load instead of pieces of many rows.  The packing is a pure
  * reordering of the elements of Wi and U (the GRU of Eq. 1 is unchanged):
  * results with and without it are bitwise identical.  An optional operand of
  * ggnn_model (gru_packed).

@@ -107,7 +107,7 @@ class BandedGGNN:
                  band_format: str = "bits", gru_pack: bool = True):
         """band_format: "bits" (1 bit per band entry; aggregate-first fused
         forward) or "dense" (band entries in the compute dtype; transform-first
-        forward).  gru_pack: hand the GRU kernels Wi, U in their staging order
+        forward).  gru_pack: hand the GRU kernels Wi, U in their fragment order
         (used at H >= 128 in bf16; results are identical either way)."""
         import torch
         self.torch = torch
@@ -161,24 +161,22 @@ class BandedGGNN:
         for s_ in sizes:
             offs.append(offs[-1] + -(-s_ // 64) * 64)
         self._layout = list(zip(offs, sizes))
-        self.master = torch.zeros((offs[-1],), dtype=torch.float32, device=device)
-        self.compute_copy = torch.zeros((offs[-1],), dtype=td, device=device) if dt == "bf16" else None
-        states = self.master if self.compute_copy is None else self.compute_copy
-        self.W = self._views(states)[0].view(E, H, H)
-        self.W.copy_(to_device(params.W, dt, device))
+        host = np.zeros((offs[-1],), np.float32)
+        for (o, n), v in zip(self._layout, (params.W, params.bias, params.Wi, params.U, params.b)):
+            if v is not None:
+                host[o:o + n] = np.asarray(v, np.float32).reshape(-1)
+        self.master = torch.from_numpy(host).to(device)
+        self.compute_copy = self.master.to(td) if dt == "bf16" else None   # exact: the values are bf16 already
+        states = self._views(self.master if self.compute_copy is None else self.compute_copy)
+        masters = self._views(self.master)
+        self.W = states[0].view(E, H, H)
         # W_e^T, an optional operand of the bit-band forward (row reads of its
         # weight fragments); refreshed from W by refresh_weights().
         self.Wt = torch.empty_like(self.W)
-        self.bias = None
-        if params.bias is not None:
-            self.bias = self._views(self.master)[1].view(E, H)
-            self.bias.copy_(torch.from_numpy(params.bias.astype(np.float32)))
-        self.Wi, self.U = (self._views(states)[i].view(H, 3 * H) for i in (2, 3))
-        self.Wi.copy_(to_device(params.Wi, dt, device))
-        self.U.copy_(to_device(params.U, dt, device))
-        self.b = self._views(self.master)[4]
-        self.b.copy_(torch.from_numpy(params.b.astype(np.float32)))
-        # Wi, U in the staging order of the large-width GRU kernels, refreshed
+        self.bias = None if params.bias is None else masters[1].view(E, H)
+        self.Wi, self.U = states[2].view(H, 3 * H), states[3].view(H, 3 * H)
+        self.b = masters[4]
+        # Wi, U in the fragment order of the large-width GRU kernels, refreshed
         # with Wt; absent where no kernel reads it.
         pk = capi.ggnn_gru_pack_bytes(dt, H) if gru_pack else 0
         self.gru_packed = torch.empty((pk,), dtype=torch.uint8, device=device) if pk else None
