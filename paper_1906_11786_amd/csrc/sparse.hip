@@ -183,6 +183,13 @@ __host__ __device__ constexpr long sparse_lds_bytes(int E) {
   return (long)E * H * H * (int)sizeof(S) + kSparseWaves * 4L * (sparse_rp_ints(E) + kSparseCols);
 }
 
+// Orders one wave's LDS accesses before and after (other lanes of the wave read what a lane wrote).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <typename S, int H>
 __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const S* __restrict__ X,
@@ -215,13 +222,15 @@ __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
     const int n0 = 16 * grp;
     const int32_t* src = row_ptr + (size_t)n0 * E;
     const int count = 16 * E + 1;
-    // Wave-private LDS: the copies below are ordered by the waits the
-    // compiler places before the reads, no barrier.
+    // Wave-private LDS: the wave's own writes and reads are kept in order by
+    // wavefront fences, no barrier.
     for (int i = lane; i < count; i += kWave) rp[i] = src[i];
+    wave_lds_order();
     const int first = __builtin_amdgcn_readfirstlane(rp[0]);
     const int total = __builtin_amdgcn_readfirstlane(rp[16 * E]) - first;
     const int kept = total < kSparseCols ? total : kSparseCols;
     for (int i = lane; i < kept; i += kWave) cl[i] = col[first + i];
+    wave_lds_order();
     auto sender = [&](int k) __attribute__((always_inline)) {   // k-th sender of the group
       return total <= kSparseCols ? cl[k] : (k < kSparseCols ? cl[k] : col[first + k]);
     };
@@ -294,6 +303,7 @@ __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
 #pragma unroll
     for (int mo = 0; mo < MT; ++mo)
       *reinterpret_cast<f32x4*>(out + (size_t)(n0 + q) * H + 16 * mo + 4 * g) = acc[mo];
+    wave_lds_order();   // this group's lists are read before the next group's are written
   }
 }
 
