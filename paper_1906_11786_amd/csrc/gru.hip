@@ -896,22 +896,30 @@ hipError_t gru_fwd_h(int n_pad, const float* a, const void* h, const void* Wi, c
   hipLaunchKernelGGL((dev::gru_fwd_cols_kernel<H, NTL, NW, PK>), dim3((n_pad + 16 * NTL * NW - 1) / (16 * NTL * NW)), \
                      dim3(H / 32 * NW * 64), 0, st, a, static_cast<const S*>(h), static_cast<const S*>(Wi),     \
                      static_cast<const S*>(U), pk, b, static_cast<S*>(h_out), static_cast<S*>(saved), n_pad)
-    // 16 nodes per workgroup while that leaves no compute unit two of them (2,048 nodes at H = 256: 15.0 us
-    // against 23.8 with 64, at H = 128: 7.8 against 9.7), else 64, so that the weights are read less often
-    // (12,352 nodes: 27 us against 52 with 16 and 36 with 32; H = 128: 12.7 / 16.7 / 13.0).
-    const bool small = H >= 128 && n_pad <= 4096;
+    // The fewest node tiles per wave that leave no compute unit two workgroups: 16, 32 or 64 nodes (times NW); above
+    // that 64, so that the weights are read less often.  One / two / four tiles, us: H = 64, 8,192 nodes 4.9 / 5.8 /
+    // 7.9, 16,384 7.3 / 6.5 / 8.6, 262,144 (nothing saved) 55 / 45 / 41; H = 32, 16,384 4.0 / 5.1 / 6.6, 32,768 5.7 /
+    // 5.6 / 7.1; H = 128, 6,400 9.4 / 7.9 / 10.3, 16,384 15.0 / 11.3 / 10.2; H = 256, 2,048 14.9 / 17.5 / 23.1, 8,192
+    // 28.5 / 20.0 / 25.5, 16,384 53 / 37 / 29.
+    constexpr int one = 256 * 16 * NW;
+    const int tiles = n_pad <= one ? 1 : (n_pad <= 2 * one ? 2 : 4);
+#define GGNN_GRU_COLS_PICK(PK) \
+  if (tiles == 1)              \
+    GGNN_GRU_COLS(1, PK);      \
+  else if (tiles == 2)         \
+    GGNN_GRU_COLS(2, PK);      \
+  else                         \
+    GGNN_GRU_COLS(4, PK);
     if constexpr (gru_big<S, H>()) {
-      if (small && pk != nullptr)
-        GGNN_GRU_COLS(1, true);
-      else if (small)
-        GGNN_GRU_COLS(1, false);
-      else if (pk != nullptr)
-        GGNN_GRU_COLS(4, true);
-      else
-        GGNN_GRU_COLS(4, false);
+      if (pk != nullptr) {
+        GGNN_GRU_COLS_PICK(true)
+      } else {
+        GGNN_GRU_COLS_PICK(false)
+      }
     } else {
-      GGNN_GRU_COLS(4, false);
+      GGNN_GRU_COLS_PICK(false)
     }
+#undef GGNN_GRU_COLS_PICK
 #undef GGNN_GRU_COLS
     return hipGetLastError();
   } else {

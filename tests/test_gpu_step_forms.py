@@ -113,10 +113,11 @@ def test_f32_step_keeps_every_bit(B):
     np.testing.assert_array_equal(host(dX), want)
 
 
-# bf16 node update: 16 nodes per workgroup up to 4,096 nodes at H >= 128, else 64 (128 at H = 64, 256 at H = 32),
-# the last workgroup partly or mostly past the end.
-@pytest.mark.parametrize("H,n", [(32, 32), (32, 288), (64, 160), (64, 4128), (128, 32), (128, 4096), (128, 4128),
-                                 (256, 96), (256, 4096), (256, 4160)])
+# bf16 node update: one, two or four tiles of 16 nodes per wave (up to 256 workgroups of the first, of the second,
+# else), by two groups of waves at H = 64 and four at H = 32; the last workgroup partly or mostly past the end.
+@pytest.mark.parametrize("H,n", [(32, 32), (32, 288), (32, 16416), (32, 32800), (64, 160), (64, 4128), (64, 8224),
+                                 (64, 16416), (128, 32), (128, 4096), (128, 4128), (128, 8224), (256, 96), (256, 4096),
+                                 (256, 4160), (256, 8224)])
 def test_gru_update_forms(H, n):
     say(f"gru_update form H={H} n={n}")
     rng = np.random.default_rng(H + n)
