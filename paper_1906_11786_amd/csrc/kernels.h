@@ -173,7 +173,7 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 //   the reverse up to 128 row tiles of 32 nodes at H = 64, B = 64 or 128 and H = 32, B = 256, where it and the GRU's
 //     own launch beat the fused step with its few waves (both directions at T = 4, H = 64, B = 128: 182 -> 163 us at
 //     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000); at smaller B (H = 64, B = 32, 2,000 nodes: 74
-//     against 77 us) and in the forward (2,000 nodes, 8 steps: 139 against 146) the fused step stays ahead;
+//     against 77 us) the fused step stays ahead, and in the forward it depends on the types (below);
 //   at H = 128 up to 1,024 tiles (T = 2, B = 128: 383 -> 145 us at 2,000 nodes, 431 -> 235 at 12,000, 500 -> 395 at
 //     30,000; 407 -> 418 at 65,000 with T = 1), at H = 256 up to 512 (B = 128, T = 1: 483 -> 400 us at 16,000 nodes,
 //     495 -> 588 at 20,000), 1,024 at B = 512 (1,090 -> 709 at 20,000; 1,367 -> 1,470 at 60,000): with more
@@ -190,6 +190,17 @@ inline bool step_direct(int dt, int n_pad, int B, int H, bool rev) {
 // 320 / 189) and the narrow kernel at H = 256 (B = 256, 60,416 nodes: 492 / 902), except at B = 512 (803 / 620).
 inline bool step_direct_no_wt(int dt, int n_pad, int B, int H) {
   return H == 128 || (H == 256 && B == 512) || step_direct(dt, n_pad, B, H, false);
+}
+
+// The forward with its GRU on small grids at H <= 64 (with and without transposed weights, the same bits): the fused step walks the types
+// one after another, the direct kernel takes up to eight side by side, but the GRU is a launch of its own (4.4 us).
+// 8 steps of 1,987 nodes, fused / direct: H = 64, B = 128: 10 types 139 / 121 us, 6 types 114 / 104, 5 types 109 / 102,
+// 4 types 100 / 101, 2 types 87 / 97 (10 types at 4,000 nodes: 145 / 124); B = 64: 10 types 119 / 110, 8 types 108 / 99,
+// 6 types 97 / 97, 5 types 94 / 96; H = 32, B = 256: 10 types 110 / 95, 8 types 99 / 86, 6 types 87 / 86, 5 types
+// 85 / 85.
+inline bool step_direct_small_fwd(int n_pad, int B, int H, int E) {
+  const bool sizes = H == 64 ? B == 64 || B == 128 : H == 32 && B == 256;
+  return sizes && n_pad / 32 <= 128 && E >= (B == 128 ? 5 : 7);
 }
 
 // 1-bit band: fused aggregate-first forward and transposed-band reverse.
@@ -217,7 +228,8 @@ inline hipError_t launch_step_fwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* W, const void* Wt, const float* bias, float* a,
                                            const void* Wi, const void* U, const float* bg, void* h_out, void* saved,
                                            bool* fused, hipStream_t st) {
-  if (Wt == nullptr ? step_direct_no_wt(dt, n_pad, B, H) : step_direct(dt, n_pad, B, H, false)) {
+  if (step_direct_small_fwd(n_pad, B, H, E) ||
+      (Wt == nullptr ? step_direct_no_wt(dt, n_pad, B, H) : step_direct(dt, n_pad, B, H, false))) {
     if (fused) *fused = false;
     return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
   }

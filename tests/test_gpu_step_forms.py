@@ -73,9 +73,11 @@ def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
 
 
 # bf16: the direct-weight kernel's three workgroup forms (up to 128 row tiles of 32 nodes, up to 512, more), both
-# sides of the sizes where another kernel takes over (H = 64: 128 tiles at B <= 128).
+# sides of the sizes where another kernel takes over (H = 64: 128 tiles at B <= 128; in the forward with its GRU
+# from 5 types on at B = 128, from 7 at B = 64 and at H = 32, B = 256).
 @pytest.mark.parametrize("B,H,E,nb,bias", [
-    (64, 64, 9, 64, True), (64, 64, 3, 65, True), (128, 64, 10, 32, False), (128, 64, 3, 33, False),
+    (64, 64, 7, 2, True), (64, 64, 6, 64, False), (128, 64, 5, 1, True), (128, 64, 4, 32, True), (256, 32, 7, 16, True),
+    (256, 32, 6, 3, False), (256, 32, 8, 17, False), (64, 64, 9, 64, True), (64, 64, 3, 65, True), (128, 64, 10, 32, False), (128, 64, 3, 33, False),
     (256, 64, 5, 3, True), (256, 64, 2, 20, False), (256, 64, 2, 65, True), (512, 32, 3, 2, True), (512, 32, 1, 33, False),
     (256, 32, 2, 16, True), (32, 128, 3, 4, True), (32, 128, 2, 520, False), (64, 128, 1, 260, True),
     (128, 128, 9, 2, False), (128, 128, 2, 40, True), (128, 128, 2, 130, True), (256, 128, 2, 17, False),
