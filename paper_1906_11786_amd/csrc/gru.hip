@@ -150,13 +150,15 @@ __global__ __launch_bounds__(WAVES * kWave) void gru_fwd_kernel(const float* __r
 // For H <= 64 the weights are staged once per workgroup in LDS (plain
 // copies: the reverse products read rows of Wi and U, contiguous in the gate
 // dimension); larger H reads their fragments from global memory (cached).
+// `dh` may be `gin` (the reverse step that runs the GRU reverse as a launch of
+// its own leaves the summed gradient where dh goes): every element is read and
+// written by the same lane, and neither pointer is qualified as unaliased.
 // ---------------------------------------------------------------------------
 template <typename S, int H, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void gru_bwd_kernel(const float* __restrict__ gin, const S* __restrict__ h,
+__global__ __launch_bounds__(WAVES * kWave) void gru_bwd_kernel(const float* gin, const S* __restrict__ h,
                                                                  const S* __restrict__ saved, const S* __restrict__ Wi,
                                                                  const S* __restrict__ U, S* __restrict__ daT,
-                                                                 float* __restrict__ dh, S* __restrict__ ghat,
-                                                                 int n_pad) {
+                                                                 float* dh, S* __restrict__ ghat, int n_pad) {
   constexpr int MTL = H / 16;
   constexpr int NT = WAVES * kWave;
   constexpr int V = 16 / sizeof(S);

@@ -220,3 +220,33 @@ def test_gru_update_bwd_forms(H, n):
     got = (host(da).T, host(dh), host(dWi), host(dU), host(db))
     for w, x in zip(want, got):
         assert relerr(x, w) <= TOL["bf16"]
+
+
+# The reverse step whose GRU reverse is a launch of its own works in place (dh_prev takes the summed gradient, then
+# dh): the same bits as with two buffers.  fp32 and small bf16 grids (gru_bwd_kernel), 32 and 64 nodes per workgroup
+# at H >= 128 with the last one partly past the end.
+@pytest.mark.parametrize("dt,B,H,n", [("f32", 32, 32, 96), ("f32", 64, 128, 8256), ("bf16", 64, 64, 4096),
+                                      ("bf16", 32, 128, 8224), ("bf16", 32, 256, 96), ("bf16", 32, 256, 8224)])
+def test_step_bits_gru_bwd_in_place(dt, B, H, n):
+    say(f"step_bits_gru_bwd in place dt={dt} B={B} H={H} n={n}")
+    E = 5
+    rng = np.random.default_rng(B + H + n)
+    k = 1 / np.sqrt(H)
+    _, bits_t, _, _, _ = capi.ggnn_banded_pack_bits(n, E, B, *_edges(rng, n, 3 * n, E, 20))
+    bits_t = torch.from_numpy(bits_t).cuda()
+    da, h = (dev(round_to(dt, rng.standard_normal(s)), dt) for s in ((H, n), (n, H)))
+    W = dev(round_to(dt, k * rng.standard_normal((E, H, H))), dt)
+    Wi, U = (dev(round_to(dt, rng.uniform(-k, k, (H, 3 * H))), dt) for _ in range(2))
+    gates = dev(round_to(dt, rng.uniform(0, 1, (n, 3 * H))), dt)
+    dX_in = dev(rng.standard_normal((n, H)))
+    dM = torch.empty((E, n, H), device="cuda", dtype=torch_dt(dt))
+    dap, dhp = torch.empty_like(da), torch.full((n, H), float("nan"), device="cuda")
+    gh = torch.empty_like(gates)
+    capi.ggnn_step_bits_gru_bwd(dt, n, B, H, E, bits_t, da, W, dX_in, dM, n, Wi, U, h, gates, dap, dhp, gh)
+    g, da2, dh2 = torch.empty_like(dX_in), torch.empty_like(da), torch.empty_like(dX_in)
+    capi.ggnn_banded_step_bits_bwd(dt, n, B, H, E, bits_t, da, W, dX_in, g, dM, n)
+    ws_n = capi.ggnn_gru_update_bwd_workspace_bytes(dt, n, H)
+    ws = torch.empty(ws_n, dtype=torch.uint8, device="cuda")
+    sums = [torch.zeros(s, device="cuda") for s in ((H, 3 * H), (H, 3 * H), (3 * H,))]
+    capi.ggnn_gru_update_bwd(dt, n, H, g, g, h, gates, Wi, U, da2, dh2, *sums, ws, ws_n)
+    assert torch.equal(dap, da2) and torch.equal(dhp, dh2)
