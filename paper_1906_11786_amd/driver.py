@@ -162,9 +162,12 @@ class BandedGGNN:
             offs.append(offs[-1] + -(-s_ // 64) * 64)
         self._layout = list(zip(offs, sizes))
         host = np.zeros((offs[-1],), np.float32)
-        for (o, n), v in zip(self._layout, (params.W, params.bias, params.Wi, params.U, params.b)):
-            if v is not None:
-                host[o:o + n] = np.asarray(v, np.float32).reshape(-1)
+        for (o, n), name in zip(self._layout, ("W", "bias", "Wi", "U", "b")):
+            if getattr(params, name) is not None:   # of more types than the graphs have, the first E are taken
+                v = np.asarray(getattr(params, name), np.float32).reshape(-1)
+                if v.size < n:
+                    raise ValueError(f"params.{name} holds {v.size} values, {n} are needed")
+                host[o:o + n] = v[:n]
         self.master = torch.from_numpy(host).to(device)
         self.compute_copy = self.master.to(td) if dt == "bf16" else None   # exact: the values are bf16 already
         states = self._views(self.master if self.compute_copy is None else self.compute_copy)
