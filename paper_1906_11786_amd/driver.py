@@ -291,6 +291,9 @@ class BandedGGNN:
         torch = self.torch
         dev = self.device
         check_candidates(cands, self.comp.n_pad)
+        w_host = np.asarray(w_out, np.float32).reshape(-1)   # of any shape with H values
+        if w_host.size != self.H:
+            raise ValueError(f"w_out holds {w_host.size} values, H={self.H} are needed")
         self.cand_node = torch.from_numpy(np.ascontiguousarray(cands.node, np.int32)).to(dev)
         self.cand_ptr = torch.from_numpy(np.ascontiguousarray(cands.ptr, np.int32)).to(dev)
         self.target = torch.from_numpy(np.ascontiguousarray(cands.target, np.int32)).to(dev)
@@ -298,7 +301,7 @@ class BandedGGNN:
         self.n_cand = int(cands.ptr[-1])
         masters = self._views(self.master)
         self.w_out, self.b_out = masters[5], masters[6]
-        self.w_out.copy_(torch.from_numpy(np.asarray(w_out, np.float32)))
+        self.w_out.copy_(torch.from_numpy(w_host))
         self.b_out.fill_(float(b_out))
         self.logits = torch.empty((max(self.n_cand, 1),), dtype=torch.float32, device=dev)
         self.dlogit = torch.empty_like(self.logits)

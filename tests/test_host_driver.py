@@ -49,3 +49,18 @@ def test_parameters_of_too_few_values_are_refused(name, calls):
         return types.SimpleNamespace(**d)
     with pytest.raises(ValueError, match=name):
         _model("f32", fewer)
+
+
+@pytest.mark.parametrize("shape", [(H,), (H, 1), (1, H)])
+def test_readout_weights_of_any_shape_with_h_values(shape, calls):
+    m, _, comp = _model("f32")
+    w, b = draw_readout(5, H)
+    m.setup_training(draw_candidates(5, comp.offsets), np.reshape(w, shape), b)
+    np.testing.assert_array_equal(m.w_out.numpy(), np.asarray(w, np.float32))
+
+
+@pytest.mark.parametrize("count", [0, 1, H - 1, H + 1])
+def test_readout_weights_of_another_count_are_refused(count, calls):
+    m, _, comp = _model("f32")
+    with pytest.raises(ValueError, match="w_out"):
+        m.setup_training(draw_candidates(5, comp.offsets), np.ones(count), 0.0)
