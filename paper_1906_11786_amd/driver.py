@@ -299,7 +299,10 @@ class BandedGGNN:
         self.target = torch.from_numpy(np.ascontiguousarray(cands.target, np.int32)).to(dev)
         self.n_graphs = len(cands.ptr) - 1
         self.n_cand = int(cands.ptr[-1])
-        masters = self._views(self.master)
+        # The first call takes the places of the flat buffer; a later one leaves the tensors of an earlier call to
+        # whoever still holds them and makes its own (train_step() then updates one parameter after another).
+        again = hasattr(self, "param_state")
+        masters = self._views(torch.zeros_like(self.master) if again else self.master)
         self.w_out, self.b_out = masters[5], masters[6]
         self.w_out.copy_(torch.from_numpy(w_host))
         self.b_out.fill_(float(b_out))
@@ -309,19 +312,21 @@ class BandedGGNN:
         ws = capi.ggnn_readout_loss_bwd_workspace_bytes(self.H, self.n_cand)
         self.readout_ws = torch.empty((max(ws, 16),), dtype=torch.uint8, device=dev)
         self.opt = dict(lr=lr, momentum=momentum, weight_decay=weight_decay, nesterov=nesterov)
-        # (master float32, velocity, gradient, compute copy or None)
         self.velocity = torch.zeros_like(self.master)
         vels = self._views(self.velocity)
         entries = [(0, self.W, self.dW), (2, self.Wi, self.dWi), (3, self.U, self.dU), (4, self.b, self.db),
                    (5, self.w_out, self.dw_out), (6, self.b_out, self.db_out)]
         if self.bias is not None:
             entries.append((1, self.bias, self.dbias))
+        # What train_step() updates: (master float32, velocity, gradient, compute copy or None) per parameter.
         self.param_state = []
         for i, t, g in entries:
             copy = t if t.dtype != torch.float32 else None
+            master = t if copy is None else masters[i].view(t.shape)
             if copy is not None:
-                masters[i].copy_(t.reshape(-1))
-            self.param_state.append((masters[i].view(t.shape), vels[i].view(t.shape), g, copy))
+                master.copy_(t)
+            self.param_state.append((master, vels[i].view(t.shape), g, copy))
+        self._flat_state = None if again else tuple(self.param_state)
 
     def readout(self, stream=None):
         """Logits, per-graph losses and d(mean loss)/d(logits) of X_T."""
@@ -341,8 +346,12 @@ class BandedGGNN:
                                    self.readout_ws.numel(), stream)
         capi.ggnn_backward(self.model, self.act, self.grads, stream)
         o = self.opt
-        capi.ggnn_sgd_momentum(self.master.numel(), self.master, self.velocity, self.grad_buf, o["lr"],
-                               o["momentum"], o["weight_decay"], o["nesterov"], self.dt, self.compute_copy, stream)
+        updates = self.param_state
+        if self._flat_state is not None:   # one launch over the flat buffers
+            updates = [(self.master, self.velocity, self.grad_buf, self.compute_copy)]
+        for master, vel, g, copy in updates:
+            capi.ggnn_sgd_momentum(master.numel(), master, vel, g, o["lr"], o["momentum"], o["weight_decay"],
+                                   o["nesterov"], self.dt, copy, stream)
         self.refresh_weights(stream)
 
     # --------------------------------------------- evaluation on every edge

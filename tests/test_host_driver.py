@@ -64,3 +64,26 @@ def test_readout_weights_of_another_count_are_refused(count, calls):
     m, _, comp = _model("f32")
     with pytest.raises(ValueError, match="w_out"):
         m.setup_training(draw_candidates(5, comp.offsets), np.ones(count), 0.0)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_a_second_setup_leaves_the_tensors_of_the_first(dt, calls):
+    m, _, comp = _model(dt)
+    cands = draw_candidates(5, comp.offsets)
+    m.setup_training(cands, np.full(H, 2.0), 3.0)
+    held = [m.w_out, m.b_out] + [st[0] for st in m.param_state if st[3] is not None] + [st[1] for st in m.param_state]
+    for t in held:
+        t.add_(0.25)   # as training does
+    want = [t.clone() for t in held]
+    m.setup_training(cands, np.full(H, 5.0), 7.0)
+    assert all(torch.equal(a, b) for a, b in zip(held, want))
+    assert (m.w_out == 5).all() and m.b_out.item() == 7 and not any(st[1].any() for st in m.param_state)
+    # the parameters of the model itself stay where they are, and the masters hold their values
+    assert m.param_state[3][0] is m.b and m.model.b == m.b.data_ptr()
+    for i, t in enumerate((m.W, m.Wi, m.U, m.b)):
+        assert torch.equal(m.param_state[i][0].to(t.dtype), t)
+    del calls[:]
+    m.train_step()
+    updates = [a for n, a in calls if n == "ggnn_sgd_momentum"]
+    assert len(updates) == len(m.param_state)
+    assert {a[1].data_ptr() for a in updates} == {st[0].data_ptr() for st in m.param_state}
