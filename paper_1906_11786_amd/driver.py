@@ -318,7 +318,8 @@ class BandedGGNN:
                    (5, self.w_out, self.dw_out), (6, self.b_out, self.db_out)]
         if self.bias is not None:
             entries.append((1, self.bias, self.dbias))
-        # What train_step() updates: (master float32, velocity, gradient, compute copy or None) per parameter.
+        # What train_step() updates: (master float32, velocity, gradient, compute copy or None) per parameter; a
+        # caller may take entries out (parameters that stay as they are) or put others in.
         self.param_state = []
         for i, t, g in entries:
             copy = t if t.dtype != torch.float32 else None
@@ -346,8 +347,9 @@ class BandedGGNN:
                                    self.readout_ws.numel(), stream)
         capi.ggnn_backward(self.model, self.act, self.grads, stream)
         o = self.opt
-        updates = self.param_state
-        if self._flat_state is not None:   # one launch over the flat buffers
+        updates, flat = self.param_state, self._flat_state
+        if flat is not None and len(updates) == len(flat) and all(a is b for a, b in zip(updates, flat)):
+            # as set up: one launch over the flat buffers
             updates = [(self.master, self.velocity, self.grad_buf, self.compute_copy)]
         for master, vel, g, copy in updates:
             capi.ggnn_sgd_momentum(master.numel(), master, vel, g, o["lr"], o["momentum"], o["weight_decay"],

@@ -87,3 +87,24 @@ def test_a_second_setup_leaves_the_tensors_of_the_first(dt, calls):
     updates = [a for n, a in calls if n == "ggnn_sgd_momentum"]
     assert len(updates) == len(m.param_state)
     assert {a[1].data_ptr() for a in updates} == {st[0].data_ptr() for st in m.param_state}
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_train_step_updates_what_param_state_holds(dt, calls):
+    """One launch for the parameters as set up; without an entry (a parameter that is to stay as it is), or with
+    another in its place, one launch per entry that is left."""
+    m, _, comp = _model(dt)
+    m.setup_training(draw_candidates(5, comp.offsets), *draw_readout(5, H))
+
+    def updated():
+        del calls[:]
+        m.train_step()
+        return [(a[1].data_ptr(), a[2].data_ptr(), a[3].data_ptr()) for n, a in calls if n == "ggnn_sgd_momentum"]
+    assert updated() == [(m.master.data_ptr(), m.velocity.data_ptr(), m.grad_buf.data_ptr())]
+    full = list(m.param_state)
+    for state in (full[1:], full[:2] + [tuple(t.clone() if isinstance(t, torch.Tensor) else t for t in full[2])] + full[3:],
+                  []):
+        m.param_state = state
+        assert updated() == [tuple(t.data_ptr() for t in st[:3]) for st in state]
+    m.param_state = full
+    assert len(updated()) == 1
