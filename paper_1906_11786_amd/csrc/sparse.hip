@@ -8,12 +8,15 @@
 //
 // in the operand order of Algorithm 1 (aggregate per type, then transform),
 // the aggregate gathered exactly from the receiver-major lists of
-// ggnn_sparse_csr.  One workgroup per 16 receivers, its waves taking turns
-// over the edge types: lane (q, g) gathers, for receiver q, features
-// 32kk + 8g .. + 7 of every sender row (the four lanes of
+// ggnn_sparse_csr.  A wave takes 16 receivers: lane (q, g) gathers, for
+// receiver q, features 32kk + 8g .. + 7 of every sender row (the four lanes of
 // a receiver read whole rows together), sums them in float32, and the
 // per-type transform runs on the matrix cores with the aggregate as the B
 // operand (bf16 hi + lo in bf16 mode) and rows of W_e^T as the A operand.
+// Two forms: one workgroup per 16 receivers, on small graphs with the types
+// dealt to its waves (sparse_step_kernel), and, on larger graphs at H <= 64,
+// one workgroup per compute unit with all types' weights in LDS
+// (sparse_lds_kernel); launch_sparse_step says where which runs.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -170,12 +173,17 @@ __global__ __launch_bounds__(NW * kWave) void sparse_step_kernel(
 // (H / 16) (H / 32) loads of 16 lines.  Here they are read from LDS in fragment
 // order, and the wave's list bounds and senders (one contiguous piece of
 // row_ptr and col each) are copied to LDS with coalesced loads, which leaves
-// the sender rows as the only gathers; the next type's first two rows per
-// receiver are in flight while a type is summed and transformed.  Sums are
-// formed in list order, as above (the results are the same bits).  100,000
-// nodes, H = 64, 10 types: 101 -> 45 us per launch.
+// the sender rows as the only gathers; the next type's first PF rows per
+// receiver are in flight while a type is summed and transformed.  A few long
+// lists in a group (a receiver that many nodes send to) are shared by the
+// wave's lanes; every other sum is formed in list order, as above.  100,000
+// nodes, H = 64, 10 types, two senders per receiver and type: 101 -> 45 us per
+// launch; with eight receivers of 2,000 more senders each 671 -> 159 us (812 without
+// the sharing), at 20,000 nodes 186 -> 91 (527).
 // ---------------------------------------------------------------------------
 constexpr int kSparseWaves = 16;      // per workgroup
+constexpr int kSparseLong = 48;       // a list of one receiver and type with more senders is shared by the wave,
+constexpr int kSparseShared = 4;      // if at most so many of the 16 receivers have one
 constexpr int kSparseCols = 448;      // senders of 16 receivers kept in LDS (others are read from memory)
 __host__ __device__ constexpr int sparse_rp_ints(int E) { return (16 * E + 1 + 63) / 64 * 64; }
 template <typename S, int H>
@@ -196,6 +204,7 @@ __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
     const S* __restrict__ Wt, const float* __restrict__ bias, float* __restrict__ out, int n_pad, int E) {
   constexpr int HK = H / 32, MT = H / 16, V = 16 / (int)sizeof(S);
   constexpr int NP = sizeof(S) == 2 ? 2 : 1;
+  constexpr int PF = HK * sizeof(S) <= 4 ? 2 : 1;   // rows in flight ahead (fp32 at H = 64: few registers left)
   __shared__ __attribute__((aligned(16))) char lds[160 * 1024];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int q = lane % 16, g = lane / 16;
@@ -239,12 +248,12 @@ __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
     for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     int lo[2], len[2];
-    frag_t<S> v[2][2][HK];   // the first two sender rows of this type and the next
+    frag_t<S> v[2][PF][HK];   // the first PF sender rows of this type and the next
     auto fetch = [&](int e, int b) __attribute__((always_inline)) {
       lo[b] = rp[q * E + e] - first;
       len[b] = rp[q * E + e + 1] - first - lo[b];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < PF; ++j) {
 #pragma unroll
         for (int kk = 0; kk < HK; ++kk) v[b][j][kk] = frag_t<S>{};
         if (j < len[b]) {
@@ -260,14 +269,55 @@ __global__ __launch_bounds__(kSparseWaves * kWave) void sparse_lds_kernel(
 #pragma unroll
       for (int kk = 0; kk < HK; ++kk)
 #pragma unroll
-        for (int x = 0; x < 8; ++x) p[kk][x] = static_cast<float>(v[b][0][kk][x]) + static_cast<float>(v[b][1][kk][x]);
-      for (int j = 2; j < len[b]; ++j) {
-        const S* row = X + (size_t)sender(lo[b] + j) * H + 8 * g;
+        for (int x = 0; x < 8; ++x) {
+          p[kk][x] = static_cast<float>(v[b][0][kk][x]);
+          if constexpr (PF == 2) p[kk][x] += static_cast<float>(v[b][1][kk][x]);
+        }
+      // PF rows at a time (a lane past its list's end adds zeros), a few long lists apart.
+      uint64_t todo = __builtin_amdgcn_ballot_w64(len[b] > kSparseLong) & 0xFFFFu;
+      if (__builtin_popcountll(todo) > kSparseShared) todo = 0;
+      const int most = (todo >> q) & 1 ? PF : len[b];
+      for (int j = PF; j < most; j += PF) {
+        frag_t<S> r[PF][HK];
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+#pragma unroll
+          for (int kk = 0; kk < HK; ++kk) r[i][kk] = frag_t<S>{};
+          if (j + i < most) {
+            const S* row = X + (size_t)sender(lo[b] + j + i) * H + 8 * g;
+#pragma unroll
+            for (int kk = 0; kk < HK; ++kk) r[i][kk] = load8(row + 32 * kk);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < PF; ++i)
+#pragma unroll
+          for (int kk = 0; kk < HK; ++kk)
+#pragma unroll
+            for (int x = 0; x < 8; ++x) p[kk][x] += static_cast<float>(r[i][kk][x]);
+      }
+      // A long list is shared by the 16 lane groups of four: group i takes rows PF + i, PF + 16 + i, ...; their sums meet
+      // in a butterfly, so that its rows are not one chain of loads behind which 15 receivers wait.
+      for (; todo != 0; todo &= todo - 1) {
+        const int r = __builtin_ctzll(todo);
+        const int rlo = __builtin_amdgcn_readlane(lo[b], r), rlen = __builtin_amdgcn_readlane(len[b], r);
 #pragma unroll
         for (int kk = 0; kk < HK; ++kk) {
-          const frag_t<S> r = load8(row + 32 * kk);
+          float part[8];
 #pragma unroll
-          for (int x = 0; x < 8; ++x) p[kk][x] += static_cast<float>(r[x]);
+          for (int x = 0; x < 8; ++x) part[x] = 0.f;
+#pragma unroll 1
+          for (int j = PF + q; j < rlen; j += 16) {
+            const frag_t<S> w = load8(X + (size_t)sender(rlo + j) * H + 8 * g + 32 * kk);
+#pragma unroll
+            for (int x = 0; x < 8; ++x) part[x] += static_cast<float>(w[x]);
+          }
+#pragma unroll
+          for (int x = 0; x < 8; ++x) {
+#pragma unroll
+            for (int off = 1; off < 16; off *= 2) part[x] += __shfl_xor(part[x], off);
+            p[kk][x] += q == r ? part[x] : 0.f;
+          }
         }
       }
 #pragma unroll
@@ -315,11 +365,20 @@ hipError_t launch_sparse_step(int n_pad, int H, int E, const int32_t* row_ptr, c
   using S = dev::dt_t;
   const int blocks = n_pad / 16;   // n_pad is a multiple of 32 (checked by the caller)
   const bool split = blocks <= GGNN_SPARSE_SPLIT_MAX_GROUPS;
-  // All weights in LDS where they fit and every compute unit gets several groups: T = 4 evaluations at H = 64 with
-  // 10 types take 149 -> 99 us at 1,250 groups, 197 -> 108 at 2,000, 526 -> 258 at 6,250, and 89 -> 94 at 500.
-  constexpr int kLdsMinGroups = 1024;
+  // All weights in LDS where they fit and the grid is large enough.  Up to 2,048 groups the other form shares 16
+  // receivers among eight waves, which counts the more the more types and edges a receiver has and the less the
+  // transform takes (H = 32).  Random senders, 0.5 / 2 / 8 / 30 per receiver and type, other form / this one, us:
+  // H = 64, E = 4 at 1,024 groups 12.7 / 9.7, 16.2 / 12.8, 27 / 25, 64 / 58; E = 10 there 19 / 17, 26 / 24, 47 / 52,
+  // 117 / 130, at 1,250 groups 24 / 18, 34 / 26, 66 / 57, 167 / 142; E = 14 at 1,250 30 / 23, 42 / 34, 81 / 74, 209 / 208.
+  // H = 32: E = 2 at 1,024 groups 6.6 / 6.0 to 24 / 24; E = 4 there 8.0 / 9.3 to 32 / 43, at 1,250 10 / 9 to 47 / 44; E = 10 at
+  // 1,250 10 / 11 to 92 / 104, at 2,048 121 / 131 with 30 per type; from 2,500 on (one wave per 16 receivers in both)
+  // faster in each.
+  auto lds_applies = [&](int HH) {
+    const int least = HH == 64 ? (E <= 4 ? 1024 : 1250) : (E <= 2 ? 1024 : (E <= 4 ? 1250 : GGNN_SPARSE_SPLIT_MAX_GROUPS + 1));
+    return blocks >= least;
+  };
 #define GGNN_SPARSE_LDS(HH)                                                                                        \
-  if (blocks >= kLdsMinGroups && dev::sparse_lds_bytes<S, HH>(E) <= 160 * 1024) {                     \
+  if (lds_applies(HH) && dev::sparse_lds_bytes<S, HH>(E) <= 160 * 1024) {                                          \
     hipLaunchKernelGGL((dev::sparse_lds_kernel<S, HH>), dim3(256), dim3(dev::kSparseWaves * 64), 0, st, row_ptr, col, \
                        static_cast<const S*>(X), static_cast<const S*>(Wt), bias, a, n_pad, E);                    \
     return hipGetLastError();                                                                                       \

@@ -145,7 +145,7 @@ def test_gru_update_forms(H, n):
     assert torch.equal(ns, out)
 
 
-# Sparse step: from 1,024 groups of 16 receivers on, all types' weights in LDS where they fit (E <= 14 at H = 64 in
+# Sparse step on grids around the sizes where all types' weights go to LDS, where they fit (E <= 14 at H = 64 in
 # bf16); uneven shares of the groups, a receiver with more senders than the LDS copy of its group holds, odd E.
 @pytest.mark.parametrize("dt,H,E,n", [("bf16", 64, 14, 16384), ("bf16", 64, 15, 16384), ("bf16", 64, 1, 16352),
                                       ("bf16", 32, 7, 20000), ("f32", 32, 11, 16416), ("f32", 64, 3, 16416)])
@@ -250,3 +250,38 @@ def test_step_bits_gru_bwd_in_place(dt, B, H, n):
     sums = [torch.zeros(s, device="cuda") for s in ((H, 3 * H), (H, 3 * H), (3 * H,))]
     capi.ggnn_gru_update_bwd(dt, n, H, g, g, h, gates, Wi, U, da2, dh2, *sums, ws, ws_n)
     assert torch.equal(dap, da2) and torch.equal(dhp, dh2)
+
+
+# Sparse step with all weights in LDS, on both sides of the grids where it starts (1,024 or 1,250 groups at H = 64, by
+# the types; 1,024, 1,250 or 2,049 at H = 32) and with long lists: up to four receivers of a group with more than 48
+# senders of one type have them shared by the wave, five and more walk theirs one by one.
+@pytest.mark.parametrize("dt,H,E,n", [("bf16", 64, 4, 16384), ("bf16", 64, 4, 16352), ("bf16", 64, 10, 20000),
+                                      ("bf16", 64, 14, 20032), ("bf16", 64, 10, 19968), ("bf16", 32, 2, 16384),
+                                      ("bf16", 32, 4, 20000), ("bf16", 32, 9, 32800), ("bf16", 32, 9, 32768),
+                                      ("f32", 32, 8, 32800), ("f32", 64, 3, 20000), ("f32", 64, 7, 33056)])
+def test_sparse_step_long_lists_integer_exact(dt, H, E, n):
+    say(f"sparse_step long lists dt={dt} H={H} E={E} n={n}")
+    rng = np.random.default_rng(H + E + n)
+    src, dst, et = [rng.integers(0, n, n)], [rng.integers(0, n, n)], [rng.integers(0, E, n)]
+
+    def senders(node, typ, count):
+        src.append(rng.choice(n, count, replace=False))
+        dst.append(np.full(count, node))
+        et.append(np.full(count, typ))
+    for q, count in enumerate((48, 49, 50, 63, 64, 65, 81)):     # receivers 32 .. 38: six long lists of one type
+        senders(32 + q, 0, count)
+    for q, count in zip((0, 7, 8, 15), (49, 64, 65, 300)):       # four of one type in the last group
+        senders(n - 16 + q, E - 1, count)
+    for typ in range(E):                                         # one receiver with long lists of every type
+        senders(n // 2 + 5, typ, 60 + 97 * typ)
+    senders(n // 2 + 16, 0, 3000)
+    src, dst, et = (np.concatenate(x) for x in (src, dst, et))
+    X = rng.integers(-2, 3, (n, H)).astype(np.float64)
+    W = rng.integers(-1, 2, (E, H, H)).astype(np.float64)
+    bias = rng.integers(-2, 3, (E, H)).astype(np.float64) if E % 2 else None
+    row_ptr, col, _ = capi.ggnn_sparse_csr(n, E, src, dst, et)
+    a = torch.full((n, H), float("nan"), device="cuda")
+    capi.ggnn_sparse_step(dt, n, H, E, torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), len(col),
+                          dev(X, dt), dev(W.transpose(0, 2, 1), dt), None if bias is None else dev(bias), a)
+    s, d, e, _ = O.dedupe_edges(src, dst, et)
+    np.testing.assert_array_equal(host(a), O.aggregate(n, s, d, e, O.msg_transform(X, W, bias)))
