@@ -257,12 +257,14 @@ def test_degenerate_graphs(case, band_format):
 
 
 @pytest.mark.parametrize("band_format", ["bits", "dense"])
-@pytest.mark.parametrize("n,B,E,H,T", [(1500, 128, 3, 128, 3), (1300, 256, 2, 256, 2)])
+@pytest.mark.parametrize("n,B,E,H,T", [(1500, 128, 3, 128, 3), (1300, 256, 2, 256, 2), (4160, 64, 2, 128, 2),
+                                       (8224, 32, 2, 128, 1), (4160, 64, 2, 256, 1), (8224, 32, 1, 256, 2)])
 def test_gru_packed_weights_equal_gathered(n, B, E, H, T, band_format):
-    """The large-width GRU kernels staging Wi, U from the packed copy give the
-    same forward and reverse results, bit for bit, as staging them straight
-    from the row-major weights; the packed copy holds every element of Wi
-    and U once in each of its two regions."""
+    """The large-width GRU kernels reading Wi, U as the packed fragments give
+    the same forward and reverse results, bit for bit, as reading the
+    row-major weights, with one, two and four node tiles per wave (up to 4,096
+    and 8,192 nodes, more) forward and two and four in reverse; the packed
+    copy holds every element of Wi and U once in each of its two regions."""
     dt = "bf16"
     say(f"gru packed vs gathered n={n} B={B} E={E} H={H} T={T} band={band_format}")
     g = scramble_graph(70 + H, 0, backbone_graph(70 + H, 0, n, E, span_mean=6.0, max_span=B))[0]
@@ -288,15 +290,17 @@ def test_gru_packed_weights_equal_gathered(n, B, E, H, T, band_format):
 
 
 @pytest.mark.parametrize("band_format", ["bits", "dense"])
-@pytest.mark.parametrize("B,H", [(128, 64), (128, 128), (64, 256)])
-def test_graph_replay_equals_eager(band_format, B, H):
+@pytest.mark.parametrize("B,H,n", [(128, 64, 1500), (128, 128, 1500), (64, 256, 1500), (128, 128, 32900)])
+def test_graph_replay_equals_eager(band_format, B, H, n):
     """The step captured as a HIP graph: every replay (with eager work and
     synchronizations between replays) gives the eager step's results bit for
-    bit, and they match the oracle.  H = 64 runs the fused step kernels,
-    H >= 128 the wide step kernels and the large-width GRU kernels (weights
-    from their packed copy)."""
-    dt, n, E, T = "bf16", 1500, 4, 3
-    say(f"graph replay band={band_format} B={B} H={H}")
+    bit, and they match the oracle.  On the bit band H = 64 with four types
+    runs the fused forward step and the direct-weight reverse step, H >= 128
+    the direct-weight kernel at 1,500 nodes and the wide step kernels at
+    32,900, with the large-width GRU kernels (weights from their packed
+    copy)."""
+    dt, E, T = "bf16", 4, 3
+    say(f"graph replay band={band_format} B={B} H={H} n={n}")
     g = scramble_graph(61, 0, backbone_graph(61, 0, n, E, span_mean=6.0, max_span=B))[0]
     m, res, out = _run_full([g], B, E, H, T, dt, 61, reorder=True, with_bias=True, band_format=band_format)
     _compare(res, out, dt)

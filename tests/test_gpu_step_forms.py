@@ -82,7 +82,12 @@ def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
     (256, 32, 2, 16, True), (32, 128, 3, 4, True), (32, 128, 2, 520, False), (64, 128, 1, 260, True),
     (128, 128, 9, 2, False), (128, 128, 2, 40, True), (128, 128, 2, 130, True), (256, 128, 2, 17, False),
     (512, 128, 1, 33, True), (32, 256, 3, 5, True), (64, 256, 2, 70, False), (128, 256, 1, 40, True),
-    (256, 256, 2, 1, True), (512, 256, 1, 2, True)])
+    (256, 256, 2, 1, True), (512, 256, 1, 2, True),
+    # above the direct-weight kernel's sizes at H >= 128: without W^T the same kernel at H = 128 and at H = 256,
+    # B = 512, the narrow kernel's streamed blocks at H = 256; with W^T and in reverse the wide kernel
+    (32, 128, 2, 1025, True), (64, 128, 1, 513, True), (128, 128, 3, 257, True), (256, 128, 1, 129, True),
+    (512, 128, 2, 65, False), (32, 256, 2, 513, True), (64, 256, 1, 257, True), (128, 256, 3, 129, True),
+    (256, 256, 1, 65, True), (256, 256, 2, 65, False), (512, 256, 2, 65, True), (512, 256, 1, 65, True)])
 def test_bf16_step_forms_integer_exact(B, H, E, nb, bias):
     say(f"bf16 step form B={B} H={H} E={E} nb={nb} bias={bias}")
     _step_case("bf16", B, H, E, nb, B + H + E, bias)
@@ -197,7 +202,7 @@ def test_parameters_keep_their_addresses(dt):
 
 
 # bf16 node reverse at H >= 128: 32 nodes per workgroup up to 8,192 nodes, else 64, the last workgroup partly past the
-# end; the upstream gradient's buffer taking dh is what the pass over several steps does.
+# end; two buffers (test_step_bits_gru_bwd_in_place has dh in the upstream gradient's).
 @pytest.mark.parametrize("H,n", [(128, 32), (128, 96), (128, 8192), (128, 8224), (256, 32), (256, 8224)])
 def test_gru_update_bwd_forms(H, n):
     say(f"gru_update_bwd form H={H} n={n}")
