@@ -9,7 +9,9 @@
 // of 32 nodes takes eight v_mfma_f32_16x16x4_f32 of 32 cycles.  The band's
 // entries are 0 or 1, exact in bf16, so the states are split instead, once,
 // when they are staged: x = hi + mid + lo with bf16 parts (8 + 8 + 8
-// significant bits, cut off, so the split is exact), and a k step is three
+// significant bits, cut off, so the split is exact; below about 2^-110 the low
+// part falls under the smallest bf16 subnormal, an error of less than 2^-133
+// of a state), and a k step is three
 // v_mfma_f32_16x16x32_bf16 of 16 cycles with float accumulation: the same
 // sums of the same values at 5.3 times the rate.  The transform by W_e stays
 // on the fp32 instructions: there both operands have 24 bits.
@@ -40,7 +42,7 @@
 namespace ggnn {
 namespace dev {
 
-template <typename S, int H, int B, int WAVES, int TG>
+template <typename S, int H, int B, int WAVES, int TG, int NTW_>
 struct DirectCfg {
   static constexpr bool F32 = sizeof(S) == 4;
   static constexpr int PARTS = F32 ? 3 : 1;
@@ -50,7 +52,7 @@ struct DirectCfg {
   static constexpr int HQB = B >= 512 || H == 32 ? 32 : (B >= 256 || H == 64 || H == 256 ? 64 : 128);
   static constexpr int HQ = F32 ? HQF : HQB;
   static constexpr int NQ = H / HQ, MQ = HQ / 16, MT = H / 16;
-  static constexpr int RPW = 32, NTW = 2;        // rows per wave, 16-row tiles per wave
+  static constexpr int NTW = NTW_, RPW = 16 * NTW;   // 16-row tiles and rows per wave
   static constexpr int R = WAVES * RPW, NT = TG * WAVES * kWave;
   static constexpr int RB = B / 32;              // bit-row bytes per lane and block (= k steps per block)
   // k order of a block's columns (as in the bf16 step kernels): contiguous
@@ -62,6 +64,8 @@ struct DirectCfg {
   // The groups' partial sums meet in LDS, one row tile at a time.
   static constexpr int RED = TG == 1 ? 0 : TG * WAVES * MT * 1024;
   static constexpr int LDS = PARTS * PLANE * 2 > RED ? PARTS * PLANE * 2 : RED;
+  // The forward with W^T is a form of its own where the registers that gathering columns of W takes would be spilled.
+  static constexpr bool WT_ARG = !F32 && H >= 128;
   // Output tiles whose weights are loaded together.
   static constexpr int GM = F32 ? (MQ >= 4 || H == 256 ? 2 : 4) : (HQ == 128 ? 2 : 4);
 };
@@ -138,15 +142,19 @@ __device__ __forceinline__ int direct_slot(int f) {
   return 32 * (f / 32) + 16 * ((w % 8) / 4) + 4 * (w / 8) + w % 4;
 }
 
-// Workgroup: R = 32 WAVES rows of block row k, TG * WAVES waves; wave w takes
-// rows 32 (w % WAVES) .. + 31 and the edge types of group w / WAVES (a
-// contiguous range).  V = X (forward, [n_pad][H]) or da (reverse,
-// [H][n_pad]); W [E][H][H]; Wt = W_e^T or NULL (forward).
-template <typename S, int H, int B, int WAVES, int TG, bool REV>
+// Workgroup: R = 16 NTW WAVES rows of block row k, TG * WAVES waves; wave w takes
+// R / WAVES of these rows and the edge types w / WAVES, w / WAVES + TG, ...
+// (dealt round robin: with fewer types than groups, or one more than a
+// multiple of them, the waves that have the most work are on different SIMDs;
+// with contiguous ranges 2 types of 8 groups fell to waves 3 and 7, which
+// share one).  V = X (forward, [n_pad][H]) or da (reverse, [H][n_pad]); W
+// [E][H][H]; Wt = W_e^T or NULL (forward: rows of W_e^T, else columns of W;
+// where the form WT says which, see DirectCfg).
+template <typename S, int H, int B, int WAVES, int TG, int NTW_, bool REV, bool WT>
 __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
     const uint8_t* __restrict__ bits, const S* __restrict__ V, const S* __restrict__ W, const S* __restrict__ Wt,
     const float* __restrict__ bias, float* out, int n_pad, int E, const float* dX_in, S* __restrict__ dM, long ldm) {
-  using C = DirectCfg<S, H, B, WAVES, TG>;
+  using C = DirectCfg<S, H, B, WAVES, TG, NTW_>;
   constexpr bool F32 = C::F32;
   constexpr int NT = C::NT, HQ = C::HQ, NQ = C::NQ, MQ = C::MQ, MT = C::MT, NTW = C::NTW, RB = C::RB, GM = C::GM;
   constexpr int ROWB = B / 8, TPR = B / C::R;
@@ -161,7 +169,6 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
   const int q = lane % 16, g = lane / 16;
   const int rw = (t % TPR) * C::R + C::RPW * wave;
   const int s_lo = (k == 0) ? 1 : 0, s_hi = (k == nb - 1) ? 1 : 2;
-  const int e_lo = tg * E / TG, e_hi = (tg + 1) * E / TG;
 
   auto load_bits = [&](int e, DirectBits<RB> (&dst)[3][NTW]) __attribute__((always_inline)) {
 #pragma unroll
@@ -250,12 +257,12 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
 
   for (int qs = 0; qs < NQ; ++qs) {
     DirectBits<RB> cur[3][NTW], nxt[3][NTW];
-    if (e_lo < e_hi) load_bits(e_lo, cur);
+    if (tg < E) load_bits(tg, cur);
     if (qs > 0) __syncthreads();   // every wave is done with the previous slice
     stage(qs);
     __syncthreads();
-    for (int e = e_lo; e < e_hi; ++e) {
-      if (e + 1 < e_hi) load_bits(e + 1, nxt);
+    for (int e = tg; e < E; e += TG) {
+      if (e + TG < E) load_bits(e + TG, nxt);
       // Weight fragments of output tile mo (A operand: row = output feature
       // 16 mo + q; fp32: k = the slice's features 16 m + 4 g + {0..3}, bf16:
       // 32 kk + 8 g + {0..7}).
@@ -265,7 +272,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
         constexpr int step = F32 ? 16 : 32;
 #pragma unroll
         for (int m = 0; m < WF; ++m) {
-          if (REV || Wt != nullptr) {
+          if (REV || (C::WT_ARG ? WT : Wt != nullptr)) {
             wf[m] = *reinterpret_cast<const u32x4*>((REV ? W : Wt) + ((size_t)e * H + o) * H + f + step * m);
           } else {   // a column of W_e
             const S* p = W + ((size_t)e * H + f + step * m) * H + o;
@@ -407,7 +414,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
             for (int j = 0; j < 4; ++j) acc[n][mo][j] += fd[n] * b4[j];
         }
       }
-      if (e + 1 < e_hi) {
+      if (e + TG < E) {
 #pragma unroll
         for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -468,50 +475,95 @@ struct DirectArgs {
   int n_pad, E;
 };
 
-template <int H, int B, int WAVES, int TG>
+enum : int { kRev = 1, kFwdWt = 2, kFwd = 4, kAll = 7 };   // the directions that a form is built for
+
+template <int H, int B, int WAVES, int TG, int FOR, int NTW = 2>
 hipError_t direct_launch(const DirectArgs& A, hipStream_t st) {
-  using C = dev::DirectCfg<S, H, B, WAVES, TG>;
+  using C = dev::DirectCfg<S, H, B, WAVES, TG, NTW>;
   const dim3 grid((unsigned)(A.n_pad / C::R)), block(C::NT);
-  if (A.rev)
-    hipLaunchKernelGGL((dev::step_direct_kernel<S, H, B, WAVES, TG, true>), grid, block, 0, st,
-                       static_cast<const uint8_t*>(A.bits), static_cast<const S*>(A.V), static_cast<const S*>(A.W),
-                       nullptr, nullptr, A.out, A.n_pad, A.E, A.dX_in, static_cast<S*>(A.dM), A.ldm);
-  else
-    hipLaunchKernelGGL((dev::step_direct_kernel<S, H, B, WAVES, TG, false>), grid, block, 0, st,
-                       static_cast<const uint8_t*>(A.bits), static_cast<const S*>(A.V), static_cast<const S*>(A.W),
-                       static_cast<const S*>(A.Wt), A.bias, A.out, A.n_pad, A.E, nullptr, nullptr, 0L);
-  return hipGetLastError();
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, static_cast<const uint8_t*>(A.bits), static_cast<const S*>(A.V),
+                       static_cast<const S*>(A.W), static_cast<const S*>(A.Wt), A.bias, A.out, A.n_pad, A.E, A.dX_in,
+                       static_cast<S*>(A.dM), A.ldm);
+    return hipGetLastError();
+  };
+  if (A.rev) {
+    if constexpr (FOR & kRev) return go(dev::step_direct_kernel<S, H, B, WAVES, TG, NTW, true, true>);
+  } else if (A.Wt != nullptr || !C::WT_ARG) {
+    if constexpr (FOR & kFwdWt) return go(dev::step_direct_kernel<S, H, B, WAVES, TG, NTW, false, true>);
+  } else {
+    if constexpr (C::WT_ARG && (FOR & kFwd)) return go(dev::step_direct_kernel<S, H, B, WAVES, TG, NTW, false, false>);
+  }
+  return hipErrorNotSupported;
 }
 
+// Rows and type groups of a workgroup, by the number of 32-row tiles: up to one tile per compute unit, one per
+// workgroup and eight type groups (a wave walks few types, and all eight stage the window); from there on as many rows
+// as leave each compute unit a workgroup, since a second round of workgroups costs as much as the first.
 #if GGNN_DT_BF16
-// As below; T = 2 passes of 8 types with one, two and four row tiles per workgroup: H = 128, B = 128: 145 / 181 / 251
-// us at 63 tiles, 257 / 235 / 308 at 375, 452 / 413 / 395 at 938 (H = 64, B = 256: 93 / 104 / 126, 151 / 129 / 152,
-// 259 / 214 / 193).
+// The aggregate, us, 4 types, eight groups / 2 tiles x 4 groups / 4 x 2: H = 64, B = 256: 8.7 / 9.6 / 12.6 at 64 tiles, 17 /
+// 10.5 / 13 at 512, 64 / 40 / 28 at 2,048; H = 128, B = 128: 12.6 / 14.7 / 22, 25 / 17 / 23, 91 / 61 / 48.  At H = 256 the
+// forward without W^T (column gathers) keeps four waves per workgroup, which leaves it 512 registers a lane (with eight
+// waves 36 to 100 of 256 are spilled): B = 256, 4 types 63 -> 38 us at 128 tiles, 96 -> 58 at 512, 320 -> 191 at 2,048.
+// At B = 32 a block is one tile: two groups (H = 128, 4 types, 768 tiles: 30 -> 25 us, four groups 32).
 template <int H, int B>
 hipError_t direct_pick(const DirectArgs& A, hipStream_t st) {
   const int tiles = A.n_pad / 32;
-  if constexpr (B >= 128) {
-    if (tiles > 512) return direct_launch<H, B, 4, 2>(A, st);
+  const bool no_wt = !A.rev && A.Wt == nullptr;
+  if constexpr (H == 32 ? B < 256 : H == 64 && B < 64) {
+    return hipErrorNotSupported;   // the fused kernel's sizes
+  } else if constexpr (H == 32 ? B == 256 : H == 64 && B < 256) {
+    return direct_launch<H, B, 1, 8, kAll>(A, st);   // up to 128 tiles
+  } else if constexpr (H == 256 && B < 512) {
+    if (no_wt) {
+      if (tiles <= 256) return direct_launch<H, B, 1, 4, kFwd>(A, st);
+      if constexpr (B == 32) {
+        return direct_launch<H, B, 1, 2, kFwd>(A, st);
+      } else {
+        if constexpr (B >= 128) {
+          if (tiles > 512) return direct_launch<H, B, 4, 1, kFwd>(A, st);
+        }
+        return direct_launch<H, B, 2, 2, kFwd>(A, st);
+      }
+    }
+    if (tiles <= 256) return direct_launch<H, B, 1, 8, kRev | kFwdWt>(A, st);   // up to 512 tiles
+    return direct_launch<H, B, B == 32 ? 1 : 2, B == 32 ? 2 : 4, kRev | kFwdWt>(A, st);
+  } else {
+    if (tiles <= (B == 512 && !A.rev ? 128 : 256)) return direct_launch<H, B, 1, 8, kAll>(A, st);
+    if constexpr (B == 32) {
+      if (no_wt && A.E > 6) return direct_launch<H, B, 1, 8, kFwd>(A, st);
+      return direct_launch<H, B, 1, 2, kAll>(A, st);
+    } else if constexpr (B == 64) {
+      if (no_wt) return direct_launch<H, B, 2, 2, kFwd>(A, st);
+      return direct_launch<H, B, 2, 4, kRev | kFwdWt>(A, st);
+    } else {
+      if (tiles <= 512) return direct_launch<H, B, 2, 4, kAll>(A, st);
+      return direct_launch<H, B, 4, 2, kAll>(A, st);
+    }
   }
-  if constexpr (B >= 64) {
-    if (tiles > 128) return direct_launch<H, B, 2, 4>(A, st);
-  }
-  return direct_launch<H, B, 1, 8>(A, st);
 }
 #else
-// Rows and type groups of a workgroup, by the number of 32-row tiles.  Few
-// tiles: one per workgroup and eight type groups, so that the compute units
-// fill up and a wave walks few types; many: more rows share a staged window.
-// The whole pass at H = 64, B = 128, 5 types with the small and the large
-// form: 112 / 145 us at 250 tiles, 154 / 161 us at 500, 246 / 205 us at 1000
-// (H = 32: 55 / 67, 65 / 72, 97 / 87; H = 128: 303 / 400, 405 / 437, 698 / 603).
+// A forward step with its GRU and a reverse step, us, eight groups / 2 tiles x 4 groups / 4 x 2, H = 64, B = 128, 10 types:
+// 65 / 81 / 116 at 256 tiles, 109 / 85 / 119 at 512, 202 / 154 / 132 at 1,024; 2 types 44 / 45 / 47, 68 / 47 / 50, 126 / 84 /
+// 62.
 template <int H, int B>
 hipError_t direct_pick(const DirectArgs& A, hipStream_t st) {
   const int tiles = A.n_pad / 32;
-  if (tiles <= 512) return direct_launch<H, B, 1, 8>(A, st);
-  if constexpr (B == 32) return direct_launch<H, B, 1, 2>(A, st);
-  if constexpr (B == 64) return direct_launch<H, B, 2, 2>(A, st);
-  if constexpr (B >= 128) return direct_launch<H, B, 4, 2>(A, st);
+  if constexpr (H == 256) {
+    // One type: 16 rows per wave, so that two waves share the transform of a tile that one would do alone (B = 32, 63
+    // tiles: the aggregate 55 -> 38 us, the reverse step 52 -> 33; 512 tiles 110 -> 57, 120 -> 58).
+    if (A.E == 1 && tiles <= 256) return direct_launch<H, B, 2, 4, kAll, 1>(A, st);
+    if (A.E == 1 && tiles <= 512) return direct_launch<H, B, B == 32 ? 2 : 4, 2, kAll, 1>(A, st);
+  }
+  if constexpr (B == 32) {   // four groups up to four types and up to 512 tiles, above that two
+    if (tiles > 512) return direct_launch<H, B, 1, 2, kAll>(A, st);
+    if (tiles > 256 || A.E <= 4) return direct_launch<H, B, 1, 4, kAll>(A, st);
+    return direct_launch<H, B, 1, 8, kAll>(A, st);
+  } else {
+    if (tiles <= 256) return direct_launch<H, B, 1, 8, kAll>(A, st);
+    if (tiles <= 512) return direct_launch<H, B, 2, 4, kAll>(A, st);
+    return direct_launch<H, B, B == 64 ? 2 : 4, 2, kAll>(A, st);
+  }
 }
 #endif
 

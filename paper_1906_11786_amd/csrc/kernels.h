@@ -2,9 +2,10 @@
 // validated by the C-ABI layer before these are called; each returns the
 // hipGetLastError() of its launches.
 //
-// Every kernel source is built twice, once per storage dtype (bf16 kernels
-// with matrix-core results kept in VGPRs, fp32 kernels with the compiler's
-// default register assignment); the launchers of each build live in
+// Every kernel source is built twice, once per storage dtype (bf16 kernels and
+// the fp32 direct-weight step with matrix-core results kept in VGPRs, the other
+// fp32 kernels with the compiler's default register assignment; wgrad_wide.hip,
+// bf16 only, may keep them in AGPRs); the launchers of each build live in
 // ggnn::impl_bf16 / ggnn::impl_f32, and the functions below pick one by dt.
 #pragma once
 
@@ -172,12 +173,14 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 //     B = 512): 657 -> 300 us for a pass at H = 64, B = 256 and 100,000 nodes, 515 -> 93 us (T = 2) at 2,000;
 //   the reverse up to 128 row tiles of 32 nodes at H = 64, B = 64 or 128 and H = 32, B = 256, where it and the GRU's
 //     own launch beat the fused step with its few waves (both directions at T = 4, H = 64, B = 128: 182 -> 163 us at
-//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000); at smaller B (H = 64, B = 32, 2,000 nodes: 74
-//     against 77 us) the fused step stays ahead, and in the forward it depends on the types (below);
-//   at H = 128 up to 1,024 tiles (T = 2, B = 128: 383 -> 145 us at 2,000 nodes, 431 -> 235 at 12,000, 500 -> 395 at
-//     30,000; 407 -> 418 at 65,000 with T = 1), at H = 256 up to 512 (B = 128, T = 1: 483 -> 400 us at 16,000 nodes,
-//     495 -> 588 at 20,000), 1,024 at B = 512 (1,090 -> 709 at 20,000; 1,367 -> 1,470 at 60,000): with more
-//     rows the wide kernel's sharing of every weight between the rows of a block pays.
+//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000); at smaller B
+//     (H = 64, B = 32, 2,000 nodes: 74 against 77 us) the fused step stays ahead, and in the forward it depends on the
+//     types (below);
+//   at H = 128 up to 1,024 tiles, at H = 256 up to 512, 1,024 at B = 512: with more rows the wide kernel's sharing of
+//     every weight between the rows of a block pays.  10 types, wide / direct, forward with its GRU, then reverse, us:
+//     H = 128, B = 128: 79 / 24, 71 / 19 at 2,048 nodes, 99 / 70, 76 / 56 at 32,768, 137 / 135, 105 / 128 at 65,536;
+//     H = 256, B = 256: 237 / 136, 168 / 121 at 16,384, 252 / 239, 170 / 200 at 24,576; B = 512: 546 / 373, 597 / 296
+//     at 32,768, 621 / 731, 614 / 601 at 65,536.
 inline bool step_direct(int dt, int n_pad, int B, int H, bool rev) {
   const int tiles = n_pad / 32;
   if (dt == GGNN_F32) return true;
@@ -305,7 +308,7 @@ inline hipError_t launch_transform_wgrad_nm(int dt, long K, int H, int E, const 
   return GGNN_DT_PICK(launch_transform_wgrad_nm, K, H, E, X, dM, ldk, dW, dbias, ws, defer, st);
 }
 
-// GRU weights packed in the staging order of the large-H kernels (bf16,
+// GRU weights packed in the fragment order of the large-H kernels (bf16,
 // H >= 128): gru_pack_bytes is 0 where no kernel reads the packed form, and
 // `packed` (NULL allowed) is then ignored by the launchers below.
 size_t gru_pack_bytes(int dt, int H);

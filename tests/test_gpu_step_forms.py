@@ -61,18 +61,22 @@ def _step_case(dt, B, H, E, nb, seed, bias):
     np.testing.assert_array_equal(host(dX), dX0 + np.einsum("eno,eho->nh", wM, W))
 
 
-# fp32: up to 512 row tiles of 32 nodes a workgroup holds one of them and eight type groups, above that several
-# rows and two groups (n = 16,640 and 16,896); fewer types than groups, one type.
+# fp32: up to 256 row tiles of 32 nodes a workgroup holds one of them and eight type groups (four at B = 32 with up to
+# four types), up to 512 two and four (one and four at B = 32), above that more rows and two groups; fewer types than
+# groups, more, one type (16 rows per wave at H = 256).
 @pytest.mark.parametrize("B,H,E,nb,bias", [
     (32, 32, 3, 520, True), (64, 64, 2, 260, False), (128, 64, 5, 130, True), (256, 32, 1, 65, False),
     (512, 64, 3, 33, True), (128, 128, 9, 2, True), (256, 256, 2, 1, False), (512, 128, 1, 2, True),
-    (32, 256, 10, 3, True), (64, 256, 2, 5, True)])
+    (32, 256, 10, 3, True), (64, 256, 2, 5, True), (32, 64, 4, 300, False), (32, 32, 5, 7, True), (32, 32, 9, 300, True),
+    (64, 32, 10, 140, False), (128, 64, 3, 70, True), (32, 256, 1, 2, True), (32, 256, 1, 257, False),
+    (64, 256, 1, 3, True), (64, 256, 1, 130, False), (64, 256, 1, 257, True), (128, 256, 1, 2, True),
+    (128, 256, 1, 65, False), (256, 256, 1, 33, True), (128, 256, 1, 129, True), (512, 256, 1, 1, False)])
 def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
     say(f"f32 step form B={B} H={H} E={E} nb={nb} bias={bias}")
     _step_case("f32", B, H, E, nb, B + H + E, bias)
 
 
-# bf16: the direct-weight kernel's three workgroup forms (up to 128 row tiles of 32 nodes, up to 512, more), both
+# bf16: the direct-weight kernel's workgroup forms (up to 256 row tiles of 32 nodes, up to 512, more), both
 # sides of the sizes where another kernel takes over (H = 64: 128 tiles at B <= 128; in the forward with its GRU
 # from 5 types on at B = 128, from 7 at B = 64 and at H = 32, B = 256).
 @pytest.mark.parametrize("B,H,E,nb,bias", [
@@ -83,8 +87,12 @@ def test_f32_step_forms_integer_exact(B, H, E, nb, bias):
     (128, 128, 9, 2, False), (128, 128, 2, 40, True), (128, 128, 2, 130, True), (256, 128, 2, 17, False),
     (512, 128, 1, 33, True), (32, 256, 3, 5, True), (64, 256, 2, 70, False), (128, 256, 1, 40, True),
     (256, 256, 2, 1, True), (512, 256, 1, 2, True),
-    # above the direct-weight kernel's sizes at H >= 128: without W^T the same kernel at H = 128 and at H = 256,
-    # B = 512, the narrow kernel's streamed blocks at H = 256; with W^T and in reverse the wide kernel
+    (64, 128, 3, 140, True), (128, 128, 9, 70, False), (32, 128, 7, 300, True), (32, 256, 2, 300, True),
+    (64, 256, 10, 130, False), (128, 256, 3, 70, True), (256, 64, 9, 33, True),
+    # one type without W^T: the narrow kernel's streamed blocks
+    (64, 128, 1, 130, True), (64, 128, 1, 128, False), (512, 64, 1, 65, True), (512, 64, 1, 64, False),
+    (64, 256, 1, 1, True), (512, 256, 1, 1, False),
+    # above the direct-weight kernel's sizes at H >= 128 with W^T and in reverse: the wide kernel
     (32, 128, 2, 1025, True), (64, 128, 1, 513, True), (128, 128, 3, 257, True), (256, 128, 1, 129, True),
     (512, 128, 2, 65, False), (32, 256, 2, 513, True), (64, 256, 1, 257, True), (128, 256, 3, 129, True),
     (256, 256, 1, 65, True), (256, 256, 2, 65, False), (512, 256, 2, 65, True), (512, 256, 1, 65, True)])
