@@ -173,7 +173,7 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 //     B = 512): 657 -> 300 us for a pass at H = 64, B = 256 and 100,000 nodes, 515 -> 93 us (T = 2) at 2,000;
 //   the reverse up to 128 row tiles of 32 nodes at H = 64, B = 64 or 128 and H = 32, B = 256, where it and the GRU's
 //     own launch beat the fused step with its few waves (both directions at T = 4, H = 64, B = 128: 182 -> 163 us at
-//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000); at smaller B
+//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000), few types apart (step_fused_small_rev); at smaller B
 //     (H = 64, B = 32, 2,000 nodes: 74 against 77 us) the fused step stays ahead, and in the forward it depends on the
 //     types (below);
 //   at H = 128 up to 1,024 tiles, at H = 256 up to 512, 1,024 at B = 512: with more rows the wide kernel's sharing of
@@ -188,6 +188,14 @@ inline bool step_direct(int dt, int n_pad, int B, int H, bool rev) {
   if (H == 64) return B >= 256 || (rev && B >= 64 && tiles <= 128);
   return tiles <= (H == 128 || B == 512 ? 1024 : 512);
 }
+// The reverse step with the GRU reverse after it at these sizes: with few types the launch saved by fusing counts for
+// more.  Fused / direct, us: H = 32, B = 256: one type 7.6 / 8.3 at 512 nodes, two 8.2 / 9.4 at 4,096, three 9.4 / 9.2;
+// H = 64 with 128 tiles, where the fused step has two waves per workgroup: B = 64 one type 10.9 / 11.9, two 11.5 / 12.1,
+// three 12.3 / 12.3; B = 128 one 12.1 / 12.8, two 12.8 / 13.1 (on fewer tiles 15.4 / 12.2 and more apart).
+inline bool step_fused_small_rev(int dt, int n_pad, int B, int H, int E) {
+  if (dt == GGNN_F32) return false;
+  return H == 32 ? B == 256 && E <= 2 : H == 64 && n_pad / 32 == 128 && E * B <= 128;
+}
 // Without the transposed weights the wide kernel does not apply, and the forward above those sizes is the direct
 // kernel at H = 128 (B = 128, 6 types, 65,536 nodes: 151 us with the narrow kernel's streamed blocks, 85 so; B = 512:
 // 320 / 189) and the narrow kernel at H = 256 (B = 256, 60,416 nodes: 492 / 902), except at B = 512 (803 / 620).
@@ -195,12 +203,14 @@ inline bool step_direct_no_wt(int dt, int n_pad, int B, int H) {
   return H == 128 || (H == 256 && B == 512) || step_direct(dt, n_pad, B, H, false);
 }
 
-// The forward with its GRU on small grids at H <= 64 (with and without transposed weights, the same bits): the fused step walks the types
-// one after another, the direct kernel takes up to eight side by side, but the GRU is a launch of its own (4.4 us).
+// The forward with its GRU on small grids at H <= 64 (with and without transposed weights, the same bits): the fused
+// step walks the types one after another, the direct kernel takes up to eight side by side, but the GRU is a launch of its own (4.4 us).
 // 8 steps of 1,987 nodes, fused / direct: H = 64, B = 128: 10 types 139 / 121 us, 6 types 114 / 104, 5 types 109 / 102,
 // 4 types 100 / 101, 2 types 87 / 97 (10 types at 4,000 nodes: 145 / 124); B = 64: 10 types 119 / 110, 8 types 108 / 99,
 // 6 types 97 / 97, 5 types 94 / 96; H = 32, B = 256: 10 types 110 / 95, 8 types 99 / 86, 6 types 87 / 86, 5 types
-// 85 / 85.
+// 85 / 85.  The line was measured at 1,987 nodes; against the fused step alone the direct one is ahead at every number of
+// nodes and types that it is taken for (H = 64, B = 128, 10 types: 512 nodes 17.0 / 13.1, 4,096 18.1 / 13.8).  The aggregate
+// alone (launch_step_fwd_bits) stays with the fused kernel: it has no GRU to launch, so the line would lie elsewhere.
 inline bool step_direct_small_fwd(int n_pad, int B, int H, int E) {
   const bool sizes = H == 64 ? B == 64 || B == 128 : H == 32 && B == 256;
   return sizes && n_pad / 32 <= 128 && E >= (B == 128 ? 5 : 7);
@@ -256,7 +266,7 @@ inline hipError_t launch_step_bwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* Wi, const void* U, const void* h_prev, const void* saved_prev,
                                            void* da_prev, float* dh_prev, void* ghat_prev, bool* fused,
                                            hipStream_t st) {
-  if (dX_out != nullptr && step_direct(dt, n_pad, B, H, true)) {
+  if (dX_out != nullptr && step_direct(dt, n_pad, B, H, true) && !step_fused_small_rev(dt, n_pad, B, H, E)) {
     if (fused) *fused = false;
     return GGNN_DT_PICK(launch_step_direct, true, n_pad, B, H, E, bits_t, da, W, nullptr, nullptr, dX_out, dX_in, dM,
                         ldm, st);
