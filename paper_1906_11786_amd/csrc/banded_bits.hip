@@ -195,9 +195,9 @@ struct BitsCfg {
   // the bf16 forms with H = 256 keep at least two waves (their one-wave
   // forms are not built: the code generator fails on them).
   static constexpr int MINW = ((sizeof(S) == 4 && H >= 128) || H >= 256) && B / RPW >= 2 ? 2 : 1;
-  // Step kernel forms that are launched: bf16 with the blocks staged whole
-  // and direct weights, and the streamed forward at H = 256 up to B = 256.
-  static constexpr bool FWD = sizeof(S) == 2 && (WDIR_ || (H == 256 && B <= 256));
+  // Step kernel forms that are launched: bf16 with the blocks staged whole and direct weights, and the streamed
+  // forward at the sizes of step_narrow_one_type (kernels.h).
+  static constexpr bool FWD = sizeof(S) == 2 && (WDIR_ || (H >= 128 && B == 64) || (H >= 64 && B == 512));
   static constexpr bool REV = sizeof(S) == 2 && WDIR_;
   // Forward, H <= 64 with the blocks staged: the transform's weight
   // fragments are read straight from global memory (L1/L2 resident, issued

@@ -196,11 +196,19 @@ inline bool step_fused_small_rev(int dt, int n_pad, int B, int H, int E) {
   if (dt == GGNN_F32) return false;
   return H == 32 ? B == 256 && E <= 2 : H == 64 && n_pad / 32 == 128 && E * B <= 128;
 }
-// Without the transposed weights the wide kernel does not apply, and the forward above those sizes is the direct
-// kernel at H = 128 (B = 128, 6 types, 65,536 nodes: 151 us with the narrow kernel's streamed blocks, 85 so; B = 512:
-// 320 / 189) and the narrow kernel at H = 256 (B = 256, 60,416 nodes: 492 / 902), except at B = 512 (803 / 620).
-inline bool step_direct_no_wt(int dt, int n_pad, int B, int H) {
-  return H == 128 || (H == 256 && B == 512) || step_direct(dt, n_pad, B, H, false);
+// Without the transposed weights the wide kernel does not apply: at H >= 128 the forward is the direct kernel on every
+// grid (the aggregate, B = 128, 4 types, 65,536 nodes: H = 128 108 -> 48 us against the narrow kernel's streamed blocks,
+// H = 256 226 -> 175), except where a single type leaves nothing to reuse of what it stages.  Narrow / direct there, us:
+// H = 256, B = 64: 21 / 23 at 8,192 nodes, 90 / 96 at 65,536, B = 512 72 / 99, 160 / 236; H = 128, B = 64 17 / 22 at
+// 32,768, B = 512 62 / 88 at 65,536; H = 64, B = 512 35 / 45 (26 / 21 at 16,384).
+inline bool step_narrow_one_type(int dt, int n_pad, int B, int H, int E) {
+  if (dt != GGNN_BF16 || E != 1) return false;
+  const int tiles = n_pad / 32;
+  if (B == 64) return H == 256 || (H == 128 && tiles > 256);
+  return B == 512 && (H == 256 || (H >= 64 && tiles > 1024));
+}
+inline bool step_direct_no_wt(int dt, int n_pad, int B, int H, int E) {
+  return !step_narrow_one_type(dt, n_pad, B, H, E) && (H >= 128 || step_direct(dt, n_pad, B, H, false));
 }
 
 // The forward with its GRU on small grids at H <= 64 (with and without transposed weights, the same bits): the fused
@@ -219,7 +227,7 @@ inline bool step_direct_small_fwd(int n_pad, int B, int H, int E) {
 // 1-bit band: fused aggregate-first forward and transposed-band reverse.
 inline hipError_t launch_step_fwd_bits(int dt, int n_pad, int B, int H, int E, const void* bits, const void* X,
                                        const void* W, const float* bias, float* a, hipStream_t st) {
-  if (step_direct_no_wt(dt, n_pad, B, H))
+  if (step_direct_no_wt(dt, n_pad, B, H, E))
     return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, nullptr, bias, a, nullptr, nullptr, 0,
                         st);
   return impl_bf16::launch_step_fwd_bits(n_pad, B, H, E, bits, X, W, bias, a, st);
@@ -242,7 +250,7 @@ inline hipError_t launch_step_fwd_bits_gru(int dt, int n_pad, int B, int H, int 
                                            const void* Wi, const void* U, const float* bg, void* h_out, void* saved,
                                            bool* fused, hipStream_t st) {
   if (step_direct_small_fwd(n_pad, B, H, E) ||
-      (Wt == nullptr ? step_direct_no_wt(dt, n_pad, B, H) : step_direct(dt, n_pad, B, H, false))) {
+      (Wt == nullptr ? step_direct_no_wt(dt, n_pad, B, H, E) : step_direct(dt, n_pad, B, H, false))) {
     if (fused) *fused = false;
     return GGNN_DT_PICK(launch_step_direct, false, n_pad, B, H, E, bits, X, W, Wt, bias, a, nullptr, nullptr, 0, st);
   }
