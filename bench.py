@@ -61,8 +61,8 @@ FP32_PEAK_TFLOPS = 157.3    # MI355X fp32 matrix cores
 
 # Roofline key -> (device kernel name fragments, sources that define it)
 KERNELS = {
-    "step_wide_fwd": (("step_wide_kernel", ", false, false>("), ["banded_wide.hip", "device_common.h"]),
-    "step_wide_rev": (("step_wide_kernel", ", true, false>("), ["banded_wide.hip", "device_common.h"]),
+    "step_wide_fwd": (("step_wide_kernel", ", false, false>("), ["banded_wide.hip", "band_frag.h", "device_common.h"]),
+    "step_wide_rev": (("step_wide_kernel", ", true, false>("), ["banded_wide.hip", "band_frag.h", "device_common.h"]),
     # step_bits_kernel<S, H, B, waves, direct weights, type groups, reverse, GRU, supernodes>
     "step_bits_gru": (("step_bits_kernel", ", false, true, false>("),
                       ["banded_bits.hip", "device_common.h", "gru_wave.h", "lds_dma.h"]),

@@ -36,6 +36,7 @@
 // bf16, 12,352 nodes, B = 64, H = 128, 7 types: 60 -> 28 us per forward and
 // 51 -> 25 us per reverse launch against the wide kernel, bound by the chain
 // of a wave's types (bit rows, products, weights).
+#include "band_frag.h"
 #include "device_common.h"
 #include "kernels.h"
 
@@ -91,14 +92,6 @@ __device__ __forceinline__ void split3x8(const float (&v)[8], u32x4 (&o)[3]) {
   }
 }
 
-__device__ __forceinline__ bf16x8 direct_bits_frag(uint32_t byte) {   // bit i -> element i (0 or 1)
-  const uint32_t x = byte * 0x8001u;
-  u32x4 w;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = (x & (0x10001u << (2 * k))) * (0x3F80u >> (2 * k));
-  return __builtin_bit_cast(bf16x8, w);
-}
-
 template <int NB> struct DirectBits {
   static constexpr int NW = NB < 4 ? 1 : NB / 4;
   uint32_t w[NW];
@@ -130,17 +123,6 @@ template <int NB> struct DirectBits {
     return c;
   }
 };
-
-__device__ __forceinline__ bool direct_any(uint32_t x) { return __builtin_amdgcn_ballot_w64(x != 0u) != 0; }
-
-// Row of feature f of a 32-feature group in bf16: tile 2j + i of group j holds
-// features 32j + 8r + 4i + {0..3} in rows 4r + {0..3}, so that a lane's sums
-// of two tiles are eight consecutive features (a fragment of the transform,
-// weight rows read 16 bytes at a time, one 16-byte store of dM).
-__device__ __forceinline__ int direct_slot(int f) {
-  const int w = f % 32;
-  return 32 * (f / 32) + 16 * ((w % 8) / 4) + 4 * (w / 8) + w % 4;
-}
 
 // Workgroup: R = 16 NTW WAVES rows of block row k, TG * WAVES waves; wave w takes
 // R / WAVES of these rows and the edge types w / WAVES, w / WAVES + TG, ...
@@ -236,14 +218,14 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
         tile_load<bf16s>(x, V + (size_t)((k - 1 + s) * B + c) * H + qs * HQ + f0, H);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          *reinterpret_cast<u32x4*>(at(s, direct_slot(f0 + j), c)) = tile_row_T<bf16s>(x, j);
+          *reinterpret_cast<u32x4*>(at(s, feature_slot(f0 + j), c)) = tile_row_T<bf16s>(x, j);
       }
     } else {
       constexpr int UB = (B / 8) * HQ;
       for (int u = tid; u < 3 * UB; u += NT) {
         const int s = u / UB, r = u % UB, f = 16 * (r / (16 * (B / 8))) + r % 16, c = 8 * ((r / 16) % (B / 8));
         if (s < s_lo || s > s_hi) continue;
-        *reinterpret_cast<u32x4*>(at(s, direct_slot(f), c)) =
+        *reinterpret_cast<u32x4*>(at(s, feature_slot(f), c)) =
             *reinterpret_cast<const u32x4*>(V + (size_t)(qs * HQ + f) * n_pad + (k - 1 + s) * B + c);
       }
     }
@@ -312,7 +294,7 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
         uint32_t any = 0u;
 #pragma unroll
         for (int n = 0; n < NTW; ++n) any |= cur[s][n].any();
-        if (!direct_any(any)) continue;   // no edge of this type from the block into the wave's rows
+        if (!wave_any(any)) continue;   // no edge of this type from the block into the wave's rows
         if constexpr (RB == 4 || RB == 8) {
 #pragma unroll
           for (int n = 0; n < NTW; ++n) bytes_to_contiguous<RB>(cur[s][n].w, godd);
@@ -324,11 +306,11 @@ __global__ __launch_bounds__(TG * WAVES * kWave) void step_direct_kernel(
             uint32_t step = 0u;
 #pragma unroll
             for (int n = 0; n < NTW; ++n) step |= cur[s][n].byte(kk);
-            if (!direct_any(step)) continue;
+            if (!wave_any(step)) continue;
           }
           bf16x8 bf[NTW];
 #pragma unroll
-          for (int n = 0; n < NTW; ++n) bf[n] = direct_bits_frag(cur[s][n].byte(kk));
+          for (int n = 0; n < NTW; ++n) bf[n] = bits_frag(cur[s][n].byte(kk));
 #pragma unroll
           for (int p = C::PARTS - 1; p >= 0; --p)   // the small parts first
 #pragma unroll

@@ -38,6 +38,7 @@
 //     banks.
 //   reverse (da feature-major in HBM): fragment order (a fragment's 64 lane
 //     vectors contiguous, 16-byte copies), features in the same order.
+#include "band_frag.h"
 #include "device_common.h"
 #include "kernels.h"
 
@@ -87,14 +88,6 @@ struct WideCfg {
   static constexpr int WPT = (H * 4 + NT - 1) / NT;   // 16-byte vectors per thread per weight unit
 };
 
-// Feature f of a slice -> its (tile, row) slot, as 16 * tile + row (tile
-// 2j + i of the 32-feature group j holds features 32j + 8r + 4i + {0..3} in
-// rows 4r + {0..3}); also its column in a forward node row, before the
-// swizzle.
-__device__ __forceinline__ int wide_slot(int f) {
-  const int w = f % 32;
-  return 32 * (f / 32) + 16 * ((w % 8) / 4) + 4 * (w / 8) + w % 4;
-}
 // Lane group and k step of block column c (a multiple of 8 for the step).
 template <bool KCONT, int GROW>
 __device__ __forceinline__ int wide_colgroup(int c) {
@@ -133,20 +126,6 @@ __device__ __forceinline__ bf16x8 tr_read8(const bf16s* a0, int pitch) {
   const v8i16 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, v);
 }
-
-// 8 bits -> 8 bf16 elements equal to 0 or 1 (bit i -> element i); see the
-// same expansion in the narrow step kernels.
-__device__ __forceinline__ bf16x8 wide_bits_frag(uint32_t byte) {
-  const uint32_t x = byte * 0x8001u;
-  u32x4 w;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = (x & (0x10001u << (2 * k))) * (0x3F80u >> (2 * k));
-  return __builtin_bit_cast(bf16x8, w);
-}
-
-// Whether any lane of the wave holds a nonzero x (the same answer in every
-// lane, so a branch on it is taken by the whole wave).
-__device__ __forceinline__ bool wide_any(uint32_t x) { return __builtin_amdgcn_ballot_w64(x != 0u) != 0; }
 
 template <int NB> struct WideBits {
   static constexpr int NW = NB < 4 ? 1 : NB / 4;
@@ -248,7 +227,7 @@ __global__ __launch_bounds__((WideCfg<H, B, REV>::NT)) void step_wide_kernel(
     } else {
       const int f = 16 * (r / (16 * (B / 8))) + r % 16, c = 8 * ((r / 16) % (B / 8));
       // fragment (kk, tile) of the block: lane group c / (B/4), k step (c % (B/4)) / 8
-      const int slot = wide_slot(f), gg = wide_colgroup<C::KCONT, GROW>(c), kk = wide_colstep<C::KCONT, GROW>(c);
+      const int slot = feature_slot(f), gg = wide_colgroup<C::KCONT, GROW>(c), kk = wide_colstep<C::KCONT, GROW>(c);
       *reinterpret_cast<u32x4*>(d + fo<bf16s>(kk * MQ + slot / 16, slot % 16 + 16 * gg, 0)) = v;
     }
   };
@@ -308,7 +287,7 @@ __global__ __launch_bounds__((WideCfg<H, B, REV>::NT)) void step_wide_kernel(
         for (int n = 0; n < NTW; ++n)
 #pragma unroll
           for (int i = 0; i < WideBits<RB>::NW; ++i) any_bits |= b[s][n].w[i];
-        if (!wide_any(any_bits)) continue;
+        if (!wave_any(any_bits)) continue;
 #pragma unroll
         for (int n = 0; n < NTW; ++n) b[s][n].to_contiguous(godd);
       }
@@ -362,7 +341,7 @@ __global__ __launch_bounds__((WideCfg<H, B, REV>::NT)) void step_wide_kernel(
         for (int n = 0; n < NTW; ++n)
 #pragma unroll
           for (int i = 0; i < WideBits<RB>::NW; ++i) any_bits |= cur[s][n].w[i];
-        if (!wide_any(any_bits)) continue;
+        if (!wave_any(any_bits)) continue;
       }
       const bf16s* xsb = xb + s * XS;
 #pragma unroll
@@ -371,11 +350,11 @@ __global__ __launch_bounds__((WideCfg<H, B, REV>::NT)) void step_wide_kernel(
           uint32_t any_step = 0;
 #pragma unroll
           for (int n = 0; n < NTW; ++n) any_step |= cur[s][n].byte(kk);
-          if (!wide_any(any_step)) continue;
+          if (!wave_any(any_step)) continue;
         }
         bf16x8 bf[NTW];
 #pragma unroll
-        for (int n = 0; n < NTW; ++n) bf[n] = wide_bits_frag(cur[s][n].byte(kk));
+        for (int n = 0; n < NTW; ++n) bf[n] = bits_frag(cur[s][n].byte(kk));
 #pragma unroll
         for (int m = 0; m < MQ; ++m) {
           bf16x8 af;
