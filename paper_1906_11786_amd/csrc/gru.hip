@@ -279,8 +279,8 @@ __global__ __launch_bounds__(256) void gru_pack_kernel(const S* __restrict__ Wi,
 // weights come straight from global memory (L2), read once per workgroup, one k step
 // ahead of use: a k step reads three fragments per 16 nodes for 16 products
 // (r, z and the a part of n together); r*h then adds its share of n in a
-// second, short loop.  Measured: 131,040 nodes at H = 256, unpacked weights,
-// 322 -> 250 us per launch (packed, 262,144 nodes: 433 -> 410), 65,536 nodes
+// second, short loop.  Measured: 131,072 nodes at H = 256, unpacked weights,
+// 298 -> 244 us per launch (packed, 262,144 nodes: 433 -> 410), 65,536 nodes
 // at H = 128 46 -> 36 us, 100,096 nodes at H = 64 35 -> 26 us; 2,048 nodes at
 // H = 256 58 -> 15 us.  Bound by the phases of a workgroup (staging, products,
 // nonlinearities), of which one runs at a time at H = 256, where the operands
