@@ -173,9 +173,11 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 //     B = 512): 657 -> 300 us for a pass at H = 64, B = 256 and 100,000 nodes, 515 -> 93 us (T = 2) at 2,000;
 //   the reverse up to 128 row tiles of 32 nodes at H = 64, B = 64 or 128 and H = 32, B = 256, where it and the GRU's
 //     own launch beat the fused step with its few waves (both directions at T = 4, H = 64, B = 128: 182 -> 163 us at
-//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000), few types apart (step_fused_small_rev); at smaller B
-//     (H = 64, B = 32, 2,000 nodes: 74 against 77 us) the fused step stays ahead, and in the forward it depends on the
-//     types (below);
+//     1,000 nodes, 184 -> 177 at 4,000, but 201 -> 223 at 8,000), few types apart (step_fused_small_rev).  Smaller blocks
+//     are left to the fused step, in the forward too, though with the types dealt round robin the direct one is ahead at
+//     H = 64, B = 32 (2,048 nodes, fused / direct: 4 types forward 9.5 / 9.1, reverse 13.5 / 11.7, 10 types 12.7 / 10.7, 16.2
+//     / 13.8) and from about seven types on at H = 32 (B = 128, 4 types 7.4 / 8.2, 8.6 / 8.4, 10 types 10.7 / 9.2, 11.7 / 9.8;
+//     B = 32, 10 types 7.1 / 7.5, 7.6 / 8.0).  In the forward of the larger ones it depends on the types (below);
 //   at H = 128 up to 1,024 tiles, at H = 256 up to 512, 1,024 at B = 512: with more rows the wide kernel's sharing of
 //     every weight between the rows of a block pays.  10 types, wide / direct, forward with its GRU, then reverse, us:
 //     H = 128, B = 128: 79 / 24, 71 / 19 at 2,048 nodes, 99 / 70, 76 / 56 at 32,768, 137 / 135, 105 / 128 at 65,536;
@@ -217,8 +219,10 @@ inline bool step_direct_no_wt(int dt, int n_pad, int B, int H, int E) {
 // 4 types 100 / 101, 2 types 87 / 97 (10 types at 4,000 nodes: 145 / 124); B = 64: 10 types 119 / 110, 8 types 108 / 99,
 // 6 types 97 / 97, 5 types 94 / 96; H = 32, B = 256: 10 types 110 / 95, 8 types 99 / 86, 6 types 87 / 86, 5 types
 // 85 / 85.  The line was measured at 1,987 nodes; against the fused step alone the direct one is ahead at every number of
-// nodes and types that it is taken for (H = 64, B = 128, 10 types: 512 nodes 17.0 / 13.1, 4,096 18.1 / 13.8).  The aggregate
-// alone (launch_step_fwd_bits) stays with the fused kernel: it has no GRU to launch, so the line would lie elsewhere.
+// nodes and types that it is taken for (H = 64, B = 128, 10 types: 512 nodes 17.0 / 13.1, 4,096 18.1 / 13.8).  With
+// the types dealt round robin it is level from four types on (B = 64, 2,048 nodes, 4 types 10.8 / 9.7), and the aggregate alone
+// (launch_step_fwd_bits), which has no GRU to launch and stays with the fused kernel, would take half the time there (10
+// types 13.4 / 7.6).
 inline bool step_direct_small_fwd(int n_pad, int B, int H, int E) {
   const bool sizes = H == 64 ? B == 64 || B == 128 : H == 32 && B == 256;
   return sizes && n_pad / 32 <= 128 && E >= (B == 128 ? 5 : 7);
