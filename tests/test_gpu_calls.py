@@ -313,7 +313,9 @@ def test_banded_step_bits_bwd_real_values(dt, B, H, E, nb):
     assert relerr(host(dX), want_dX) <= TOL[dt]
 
 
-STEP_GRU_CASES = [(128, 64, 10, 5), (64, 128, 2, 6), (32, 32, 4, 9), (256, 256, 2, 3)]
+# The last four: few types on both sides of the sizes where the reverse with its GRU is fused on small grids.
+STEP_GRU_CASES = [(128, 64, 10, 5), (64, 128, 2, 6), (32, 32, 4, 9), (256, 256, 2, 3), (256, 32, 2, 3), (256, 32, 3, 3),
+                  (64, 64, 2, 64), (128, 64, 1, 32)]
 
 
 # The wide step kernel's sizes (bf16, W_e^T given in the forward): more than 1,024 row tiles of 32 nodes at H = 128 and
